@@ -241,6 +241,9 @@ struct DeviceWindow {
   // the lean kernel for scores of plans read from HBM, when the window
   // qualifies (lean.ok)
   wfp::LeanParams lean{};
+  // WF_PLAN_PACK=full: every launch takes the most plans per wave (tests use
+  // it to cover small batches in the shape of large ones)
+  bool pack_full = false;
 };
 
 }  // namespace
@@ -998,13 +1001,6 @@ void plan_lean(wf_plan_ctx* ctx, const HostWindow& h, const wfp::ScoreParams& sp
   const int waves = std::min(wfp::kLeanWaves, fit);
   if (waves < 2) return;
   lp.G = G;
-  lp.waves = waves;
-  lp.lds_bytes = t.lds_bytes + waves * wb;
-  lp.grid = ctx->n_cu * std::max(1, lds_cu / lp.lds_bytes);
-  lp.xwaves = std::min(wfp::kLeanPlainWaves, fit);
-  lp.xlds_bytes = t.lds_bytes + lp.xwaves * wb;
-  lp.xgrid = ctx->n_cu * std::max(1, lds_cu / lp.xlds_bytes);
-  lp.wo = o;
   lp.checked = checked ? 1 : 0;
   lp.qbits = paper ? -1 : sp.queue;
   lp.rcap = h.rcap.empty() ? 0 : 1;
@@ -1016,18 +1012,83 @@ void plan_lean(wf_plan_ctx* ctx, const HostWindow& h, const wfp::ScoreParams& sp
   lp.search_ok = N >= 1 + 4 * wfp::kPatchMaxMut ? 1 : 0;
 }
 
-// The lean kernel's launch over n plans: the grid never exceeds the groups
-// there are.
-wfp::LeanParams lean_grid(wfp::LeanParams lp, int64_t n) {
-  const int64_t groups = (n + lp.G - 1) / lp.G;
-  const int64_t wgs = (groups + lp.waves - 1) / lp.waves;
-  if (wgs < lp.grid) lp.grid = (int)wgs;
+// Plans per wave and waves per workgroup for n plans.  A wave's time hardly
+// falls with fewer waves beside it and is mostly a serial chain (the longest
+// device of its plans, and passes that loop over its plans), so a batch too
+// small to fill the chip takes the fewest plans per wave at which every
+// group still runs at once, up to eight waves per CU (two per SIMD), and its
+// waves are spread over all CUs; a larger one takes every lane (G = gmax).
+// `fit(G)`: waves of one workgroup that fit its LDS at G plans each;
+// `most`: waves the launch may have at all.
+// Measured on MI355X, scores of 512 plans of 16 activations on 3 devices:
+// 47 us at 21 plans per wave in 3 workgroups, 19 us at one plan per wave;
+// 4,096 plans of 256 activations on 8 devices 56 us at 8, 51 us at 4 and
+// 104 us at 1 plan per wave (16 waves per CU: a second round).
+struct Shape {
+  int G, waves, grid;
+};
+template <typename F>
+Shape fit_shape(const wf_plan_ctx* ctx, int gmax, int64_t most, int64_t n, F&& fit) {
+  const int n_cu = ctx->n_cu;
+  int G = gmax;
+  for (int g = ctx->dw.pack_full ? gmax : 1; g < gmax; ++g) {
+    const int64_t at_once = std::min<int64_t>(most, (int64_t)n_cu * std::min(8, fit(g)));
+    if ((n + g - 1) / g <= at_once) {
+      G = g;
+      break;
+    }
+  }
+  const int64_t groups = (n + G - 1) / G;
+  const int w = (int)std::min<int64_t>(fit(G), (groups + n_cu - 1) / n_cu);
+  return {G, w, (int)std::min((groups + w - 1) / w, most / w)};
+}
+
+// The lean kernel's launch over n plans.
+wfp::LeanParams lean_shape(const wf_plan_ctx* ctx, int64_t n) {
+  wfp::LeanParams lp = ctx->dw.lean;
+  const int lds_blk = std::min(ctx->lds_per_block, std::min(ctx->lds_per_cu, 160 * 1024));
+  auto wave_bytes = [&](int G) {
+    wfp::LeanOffsets o{};
+    return lean_layout(ctx->host, G, ctx->dw.sp.nwa, o);
+  };
+  const int max_waves = lp.paper ? wfp::kLeanWaves : wfp::kLeanPlainWaves;
+  auto fit = [&](int G) { return std::min(max_waves, (lds_blk - lp.t.lds_bytes) / wave_bytes(G)); };
+  const Shape s = fit_shape(ctx, lp.G, (int64_t)ctx->n_cu * fit(lp.G), n, fit);
+  lp.G = s.G;
+  lp.waves = s.waves;
+  lp.grid = s.grid;
+  lp.lds_bytes = lp.t.lds_bytes + s.waves * lean_layout(ctx->host, s.G, ctx->dw.sp.nwa, lp.wo);
   return lp;
 }
 
-// Launch parameters of one pass over n plans: the grid never exceeds the
-// groups there are.
-wfp::ScoreParams fit_grid(wfp::ScoreParams sp, int64_t n) {
+// Launch parameters of one pass of the general kernel over n plans: fewer
+// plans per wave for a batch that does not fill the chip (fit_shape), else
+// the window's plan with the grid cut to the groups there are.
+wfp::ScoreParams fit_grid(const wf_plan_ctx* ctx, wfp::ScoreParams sp, bool search, int64_t n) {
+  const HostWindow& h = ctx->host;
+  const int tsz = sp.time64 ? 8 : 4;
+  const int lds_blk = std::min(ctx->lds_per_block, std::min(ctx->lds_per_cu, 160 * 1024));
+  const int wg_bytes = (sp.tab_in_lds ? sp.t.bytes : 0) + sp.wg_ld;
+  auto layout = [&](int G, wfp::WaveOffsets& o) {
+    if (sp.ring == 1) return ring_layout(h, sp, G, tsz, sp.nwa, search, o);
+    wave_layout(h, G, tsz, sp.nwa, sp.nibble, search, o, sp.wave_global != 0,
+                sp.ring == 2 ? sp.ring_size : 0);
+    return sp.wave_global ? o.split : o.bytes;
+  };
+  // (never more waves than planned: regions in HBM are sized for those)
+  const int64_t most = (int64_t)sp.grid * sp.waves;
+  if (n < most * sp.G) {
+    const int max_waves = sp.wave_global ? sp.waves : 8;
+    const Shape s = fit_shape(ctx, sp.G, most, n, [&](int G) {
+      wfp::WaveOffsets o{};
+      return std::min(max_waves, (lds_blk - wg_bytes) / std::max(layout(G, o), 1));
+    });
+    sp.G = s.G;
+    sp.waves = s.waves;
+    sp.grid = s.grid;
+    sp.lds_bytes = wg_bytes + s.waves * layout(s.G, sp.wo);
+    return sp;
+  }
   const int64_t groups = (n + sp.G - 1) / sp.G;
   const int64_t wgs = (groups + sp.waves - 1) / sp.waves;
   if (wgs < sp.grid) sp.grid = (int)wgs;
@@ -1039,11 +1100,12 @@ wfp::ScoreParams fit_grid(wfp::ScoreParams sp, int64_t n) {
 // flagged (same stream, so in order).  Generated candidates with more than
 // kPatchMaxMut mutations take the layout that holds whole rows.
 template <typename F>
-hipError_t two_pass(const DeviceWindow& dw, bool search, int64_t n, F&& launch, int32_t n_mut = 0) {
+hipError_t two_pass(const wf_plan_ctx* ctx, bool search, int64_t n, F&& launch, int32_t n_mut = 0) {
+  const DeviceWindow& dw = ctx->dw;
   const wfp::ScoreParams& s =
       !search ? dw.sp : (n_mut <= wfp::kPatchMaxMut ? dw.sp_search : dw.sp_search_wide);
-  hipError_t e = launch(fit_grid(s, n));
-  if (e == hipSuccess && dw.checked) e = launch(fit_grid(search ? dw.sp64_search : dw.sp64, n));
+  hipError_t e = launch(fit_grid(ctx, s, search, n));
+  if (e == hipSuccess && dw.checked) e = launch(fit_grid(ctx, search ? dw.sp64_search : dw.sp64, search, n));
   return e;
 }
 
@@ -1250,6 +1312,8 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
     }
     dw.lean.tab = static_cast<const unsigned char*>(dw.tab_lean);
   }
+  const char* pack = std::getenv("WF_PLAN_PACK");
+  dw.pack_full = pack && std::strcmp(pack, "full") == 0;
   dw.sp = sp;
   dw.sp_search = sps;
   dw.sp_search_wide = spsw;
@@ -1281,10 +1345,8 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
                  "ahead, %d behind); order and slot arrays in HBM\n", sp.ring_size, sp.ring_a,
                  sp.ring_b);
   if (std::getenv("WF_PLAN_VERBOSE") && dw.lean.ok)
-    std::fprintf(stderr, "[wf_plan] lean kernel: G=%d waves/wg=%d (queue variants %d) grid=%d (%d) "
-                 "tables=%d B wave=%d B lds/wg=%d (%d)\n",
-                 dw.lean.G, dw.lean.waves, dw.lean.xwaves, dw.lean.grid, dw.lean.xgrid,
-                 dw.lean.t.bytes, dw.lean.wo.bytes, dw.lean.lds_bytes, dw.lean.xlds_bytes);
+    std::fprintf(stderr, "[wf_plan] lean kernel: at most %d plans per wave, tables=%d B (%d B in LDS)\n",
+                 dw.lean.G, dw.lean.t.bytes, dw.lean.t.lds_bytes);
   free_device_window(ctx->dw);
   ctx->dw = dw;
   ctx->host = std::move(h);
@@ -1317,17 +1379,14 @@ wf_status wf_plan_score_batch(wf_plan_ctx* ctx, const int8_t* dev, const uint16_
   if (!sched && dw.lean.ok) {
     // the lean kernel, then (times not proven below 2^32) the general fp64
     // pass over the groups holding a plan whose times saturated
-    wfp::LeanParams lp = dw.lean;
-    const int64_t groups = (n_plans + lp.G - 1) / lp.G;
-    const int64_t wgs = (groups + lp.waves - 1) / lp.waves;
-    if (wgs < lp.grid) lp.grid = (int)wgs;
+    const wfp::LeanParams lp = lean_shape(ctx, n_plans);
     e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_plans, scores, nullptr, false,
                                static_cast<hipStream_t>(hip_stream));
     if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score(fit_grid(dw.sp64, n_plans), dev, prio, flags, n_plans, scores, nullptr,
+      e = wfp::launch_score(fit_grid(ctx, dw.sp64, false, n_plans), dev, prio, flags, n_plans, scores, nullptr,
                             nullptr, static_cast<hipStream_t>(hip_stream));
   } else {
-    e = two_pass(dw, false, n_plans, [&](const wfp::ScoreParams& sp) {
+    e = two_pass(ctx, false, n_plans, [&](const wfp::ScoreParams& sp) {
       return wfp::launch_score(sp, dev, prio, flags, n_plans, scores, sched, nullptr,
                                static_cast<hipStream_t>(hip_stream));
     });
@@ -1384,18 +1443,15 @@ wf_status wf_plan_search_batch(wf_plan_ctx* ctx, const int8_t* dev, const uint16
     // the lean kernel generates the candidates as the incumbent plus their
     // changed sites; then (times not proven below 2^32) the general fp64
     // pass over the groups holding a candidate whose times saturated
-    wfp::LeanParams lp = dw.lean;
-    const int64_t groups = (n_candidates + lp.G - 1) / lp.G;
-    const int64_t wgs = (groups + lp.waves - 1) / lp.waves;
-    if (wgs < lp.grid) lp.grid = (int)wgs;
+    const wfp::LeanParams lp = lean_shape(ctx, n_candidates);
     e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_candidates, scores, &sa, false,
                                static_cast<hipStream_t>(hip_stream));
     if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score(fit_grid(dw.sp64_search, n_candidates), dev, prio, flags, n_candidates,
+      e = wfp::launch_score(fit_grid(ctx, dw.sp64_search, true, n_candidates), dev, prio, flags, n_candidates,
                             scores, nullptr, &sa, static_cast<hipStream_t>(hip_stream));
   } else {
     e = two_pass(
-        dw, true, n_candidates,
+        ctx, true, n_candidates,
         [&](const wfp::ScoreParams& sp) {
           return wfp::launch_score(sp, dev, prio, flags, n_candidates, scores, nullptr, &sa,
                                    static_cast<hipStream_t>(hip_stream));
@@ -1504,14 +1560,14 @@ wf_status wf_plan_score_keys(wf_plan_ctx* ctx, const int8_t* dev, const uint16_t
   if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper) {
     // the lean kernel's key mode, then the general fp64 pass over the groups
     // holding a plan whose uint32 times saturated
-    const wfp::LeanParams lp = lean_grid(dw.lean, n_plans);
+    const wfp::LeanParams lp = lean_shape(ctx, n_plans);
     e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_plans, keys, nullptr, true,
                                static_cast<hipStream_t>(hip_stream));
     if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score_keys(fit_grid(dw.sp64, n_plans), dev, prio, flags, n_plans, keys,
+      e = wfp::launch_score_keys(fit_grid(ctx, dw.sp64, false, n_plans), dev, prio, flags, n_plans, keys,
                                  nullptr, static_cast<hipStream_t>(hip_stream));
   } else {
-    e = two_pass(dw, false, n_plans, [&](const wfp::ScoreParams& sp) {
+    e = two_pass(ctx, false, n_plans, [&](const wfp::ScoreParams& sp) {
       return wfp::launch_score_keys(sp, dev, prio, flags, n_plans, keys, nullptr,
                                     static_cast<hipStream_t>(hip_stream));
     });
@@ -1537,15 +1593,15 @@ wf_status wf_plan_search_keys(wf_plan_ctx* ctx, const int8_t* dev, const uint16_
   const DeviceWindow& dw = ctx->dw;
   if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper && dw.lean.search_ok &&
       n_mut <= wfp::kPatchMaxMut) {
-    const wfp::LeanParams lp = lean_grid(dw.lean, n_candidates);
+    const wfp::LeanParams lp = lean_shape(ctx, n_candidates);
     e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_candidates, keys, &sa, true,
                                static_cast<hipStream_t>(hip_stream));
     if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score_keys(fit_grid(dw.sp64_search, n_candidates), dev, prio, flags,
+      e = wfp::launch_score_keys(fit_grid(ctx, dw.sp64_search, true, n_candidates), dev, prio, flags,
                                  n_candidates, keys, &sa, static_cast<hipStream_t>(hip_stream));
   } else {
     e = two_pass(
-        dw, true, n_candidates,
+        ctx, true, n_candidates,
         [&](const wfp::ScoreParams& sp) {
           return wfp::launch_score_keys(sp, dev, prio, flags, n_candidates, keys, &sa,
                                         static_cast<hipStream_t>(hip_stream));

@@ -218,7 +218,7 @@ struct LeanParams {
   int ok;          // 1: the window qualifies and a layout fits in LDS
   int checked;     // 1: uint32 additions saturate and flag the plan for the fp64 pass
   int qbits;       // reclamation queue width: 32 or 64; -1: no queue (the paper's order)
-  int G, waves, grid, lds_bytes;
+  int G, waves, grid, lds_bytes;  // G: most plans per wave; the launch sets all four and wo
   const unsigned char* tab;  // the lean table image in HBM
   LeanTab t;
   LeanOffsets wo;  // wave regions follow the image's LDS part
@@ -227,9 +227,6 @@ struct LeanParams {
   int rcap;        // 1: the window caps replicas (checked per level)
   int batch;       // 1: devices with batch limits (plan scores only)
   int paper;       // 1: the paper's reclamation order (plan scores only; qbits -1)
-  // the variants with the reclamation queue are built for three waves per
-  // SIMD: up to kLeanPlainWaves waves per workgroup, their own launch
-  int xwaves, xgrid, xlds_bytes;
 };
 
 // Waves per workgroup of the lean kernel: the queue variants, and the

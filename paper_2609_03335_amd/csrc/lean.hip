@@ -1063,17 +1063,9 @@ hipError_t launch_lean_variant(const ScoreParams& sp, const LeanParams& lp, cons
                                const uint16_t* prio, const uint8_t* flags, int64_t n_plans,
                                wf_plan_score* scores, const SearchArgs& sa, hipStream_t stream) {
   auto k = score_lean<CHECKED, QB, SEARCH, PHI, RCAP, BATCH>;
-  LeanParams l = lp;
-  if (lean_plain<SEARCH, PHI, RCAP, BATCH, QB>()) {
-    // the plain variant's own launch, its grid fitted to the plans
-    l.waves = lp.xwaves;
-    l.lds_bytes = lp.xlds_bytes;
-    const int64_t wgs = ((n_plans + lp.G - 1) / lp.G + l.waves - 1) / l.waves;
-    l.grid = wgs < lp.xgrid ? (int)wgs : lp.xgrid;
-  }
   (void)hipFuncSetAttribute(reinterpret_cast<const void*>(k),
-                            hipFuncAttributeMaxDynamicSharedMemorySize, l.lds_bytes);
-  hipLaunchKernelGGL(k, dim3(l.grid), dim3(64 * l.waves), l.lds_bytes, stream, sp, l, dev, prio,
+                            hipFuncAttributeMaxDynamicSharedMemorySize, lp.lds_bytes);
+  hipLaunchKernelGGL(k, dim3(lp.grid), dim3(64 * lp.waves), lp.lds_bytes, stream, sp, lp, dev, prio,
                      flags, n_plans, scores, sa);
   return hipGetLastError();
 }
