@@ -54,8 +54,9 @@
  *     are reported on return as WF_EHIP.
  *   - A context is not thread-safe; use one per host thread.  Calls on one
  *     context must not run concurrently on different streams: the scoring
- *     calls may share the context's scratch area (per-wave regions of
- *     windows too large for LDS, allocated at upload, at most 1 GiB) and
+ *     calls may share the context's scratch areas (per-wave regions of
+ *     windows too large for LDS, at most 1 GiB, and of large batches, at most
+ *     512 MiB and kept from upload to upload; both allocated at upload) and
  *     the argmins its work area.  A new upload must not race with queued
  *     work either (synchronise first).  Use one context per stream for
  *     concurrent scoring.

@@ -12,7 +12,8 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB_NAME = "libwfplan.so"
 LIB_PATH = os.path.join(PKG, LIB_NAME)
-SOURCES = ["host.hip", "score.hip", "score_keys.hip", "argmin.hip", "prefix.hip", "lean.hip"]
+SOURCES = ["host.hip", "score.hip", "score_keys.hip", "argmin.hip", "prefix.hip", "lean.hip",
+           "lanes.hip"]
 ARCH = "gfx950"
 
 HIP_FLAGS = [

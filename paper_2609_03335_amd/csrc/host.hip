@@ -222,13 +222,10 @@ wf_status validate(const wf_window_desc* w, std::string* err, HostWindow* out) {
 }
 
 struct DeviceWindow {
-  void* tab = nullptr;          // table image in HBM
-  void* rules = nullptr;        // rule tables of the candidate generator
+  void* tab = nullptr;          // every table image of the window, in HBM
   const unsigned long long* rule_pf = nullptr;
   const int8_t* rule_best = nullptr;
-  void* tab64 = nullptr;        // fp64-time table image of the rescoring pass
   void* scratch = nullptr;      // per-wave regions for windows too big for LDS
-  void* tab_lean = nullptr;     // the lean kernel's table image
   wfp::ScoreParams sp{};        // scoring plans read from HBM
   wfp::ScoreParams sp_search{}; // scoring candidates generated around an incumbent
   // the same with more than kPatchMaxMut mutations when sp_search keeps
@@ -241,6 +238,9 @@ struct DeviceWindow {
   // the lean kernel for scores of plans read from HBM, when the window
   // qualifies (lean.ok)
   wfp::LeanParams lean{};
+  // the lane-per-plan kernel, for large batches
+  wfp::LanesParams lanes{};
+  int lanes_force = 0;          // WF_PLAN_LANES: 1 = on (any batch), -1 = off
   // WF_PLAN_PACK=full: every launch takes the most plans per wave (tests use
   // it to cover small batches in the shape of large ones)
   bool pack_full = false;
@@ -258,6 +258,10 @@ struct wf_plan_ctx {
   HostWindow host;
   DeviceWindow dw;
   void* key_work = nullptr;  // partial results of the argmins
+  // the lane-per-plan kernel's resource orders; grows with the windows
+  // uploaded, freed with the context
+  void* lanes_scratch = nullptr;
+  size_t lanes_bytes = 0;
 };
 
 namespace {
@@ -269,10 +273,7 @@ wf_status hip_fail(wf_plan_ctx* ctx, hipError_t e, const char* what) {
 
 void free_device_window(DeviceWindow& dw) {
   if (dw.tab) (void)hipFree(dw.tab);
-  if (dw.tab64) (void)hipFree(dw.tab64);
   if (dw.scratch) (void)hipFree(dw.scratch);
-  if (dw.tab_lean) (void)hipFree(dw.tab_lean);
-  if (dw.rules) (void)hipFree(dw.rules);
   dw = DeviceWindow{};
 }
 
@@ -1012,6 +1013,346 @@ void plan_lean(wf_plan_ctx* ctx, const HostWindow& h, const wfp::ScoreParams& sp
   lp.search_ok = N >= 1 + 4 * wfp::kPatchMaxMut ? 1 : 0;
 }
 
+// Slots of a plan's live times for the lane-per-plan kernel, and the
+// operations over them before each level.  A time is live from the first
+// level that may write it (a fused chain's members are finished with the
+// chain's head) to its last reader; the slot of a dead one is given to the
+// next (lowest free slot first), so a plan needs about as many as its widest
+// level has activations.
+//   - one predecessor: the release is that predecessor's finish, in place;
+//   - finishes with one reader, the same one for several, are maxed straight
+//     into the reader's release;
+//   - else the reader's release is computed from its predecessors' finishes
+//     before its level;
+//   - a finish takes the slot of its activation's own release (maxed into it:
+//     it is later) when nothing else reads that.
+struct TimeSlots {
+  std::vector<uint16_t> rel, fin;  // per activation: slot of its release, of its finish
+  std::vector<uint32_t> op;
+  std::vector<int32_t> ooff;
+  int slots = 0, n_zero = 0;
+};
+TimeSlots time_slots(const HostWindow& h) {
+  const int N = h.N, L = h.n_levels;
+  TimeSlots t;
+  t.rel.assign((size_t)N, 0);
+  t.fin.assign((size_t)N, 1);
+  const bool per_wf = (95 * h.W + 99) / 100 < h.W;  // p95 needs each workflow's latest finish
+  t.n_zero = 2 + (per_wf ? h.W : 0);
+  std::vector<int32_t> lvl((size_t)N), born((size_t)N), out((size_t)N, 0), next((size_t)N, -1);
+  std::vector<uint8_t> wf_succ((size_t)N, 0), npred_many((size_t)N, 0);
+  for (int l = 0; l < L; ++l)
+    for (int i = h.level_off[l]; i < h.level_off[l + 1]; ++i) lvl[i] = l;
+  for (int v = 0; v < N; ++v) {
+    const int b = h.pred_off[v], e = h.pred_off[v + 1];
+    born[v] = h.fusible[v] ? born[h.pred_idx[b]] : lvl[v];
+    npred_many[v] = e - b > 1;
+    for (int k = b; k < e; ++k) {
+      const int u = h.pred_idx[k];
+      ++out[u];
+      next[u] = v;
+      if (h.act_wf[u] == h.act_wf[v]) wf_succ[u] = 1;
+    }
+  }
+  // how each finish is kept: 0 nobody reads it, 1 maxed into its reader's
+  // release, 2 maxed into its workflow's latest finish, 3 a slot of its own
+  std::vector<uint8_t> kind((size_t)N);
+  std::vector<int32_t> last_walk((size_t)N, -1), last_op((size_t)N, -1);
+  // activations whose finish takes the slot of their release
+  std::vector<uint8_t> shares((size_t)N, 0), taken((size_t)N, 0);
+  std::vector<int32_t> pushers((size_t)N, 0);
+  auto pushes = [&](int u) {
+    return out[u] == 1 && npred_many[next[u]] && !(per_wf && !wf_succ[u]);
+  };
+  for (int u = 0; u < N; ++u)
+    if (pushes(u)) ++pushers[next[u]];
+  for (int u = 0; u < N; ++u) {
+    const bool wf = per_wf && !wf_succ[u];
+    kind[u] = out[u] == 0 ? (wf ? 2 : 0) : (pushes(u) && pushers[next[u]] > 1 ? 1 : 3);
+    if (kind[u] == 2) t.fin[u] = (uint16_t)(2 + h.act_wf[u]);
+    if (kind[u] == 3 && wf) last_op[u] = lvl[u] + 1;
+  }
+  std::vector<int32_t> acc_born((size_t)N, -1);  // a release maxed into: its first writer's level
+  for (int v = 0; v < N; ++v)
+    for (int k = h.pred_off[v]; k < h.pred_off[v + 1]; ++k) {
+      const int u = h.pred_idx[k];
+      if (kind[u] == 1) {
+        acc_born[v] = acc_born[v] < 0 ? born[u] : std::min(acc_born[v], born[u]);
+      } else if (npred_many[v]) {
+        last_op[u] = std::max(last_op[u], lvl[v]);
+      } else {
+        last_walk[u] = std::max(last_walk[u], lvl[v]);
+      }
+    }
+  for (int v = 0; v < N; ++v) {
+    if (kind[v] != 3 || h.pred_off[v] == h.pred_off[v + 1]) continue;
+    const int u = h.pred_idx[h.pred_off[v]];
+    // (one predecessor: its finish, when v alone reads it)
+    shares[v] = npred_many[v] || (kind[u] == 3 && out[u] == 1 && last_op[u] < 0);
+    if (shares[v] && !npred_many[v]) taken[u] = 1;
+  }
+  // per level: finishes and releases that start there
+  std::vector<std::vector<int32_t>> start((size_t)L), wf_at((size_t)L + 2);
+  std::vector<std::vector<uint16_t>> dead((size_t)L + 2);  // slots free before the level's operations
+  for (int u = 0; u < N; ++u) {
+    if (kind[u] == 3 && !shares[u]) start[born[u]].push_back(u);
+    if (acc_born[u] >= 0) start[acc_born[u]].push_back(N + u);
+    if (kind[u] == 3 && per_wf && !wf_succ[u]) wf_at[lvl[u] + 1].push_back(u);
+  }
+  std::vector<uint64_t> used(1, 0);
+  int top = 0;
+  auto alloc = [&]() -> uint16_t {
+    for (size_t w = 0;; ++w) {
+      if (w == used.size()) used.push_back(0);
+      if (~used[w]) {
+        const int b = __builtin_ctzll(~used[w]);
+        used[w] |= 1ull << b;
+        const int s = (int)w * 64 + b + t.n_zero;
+        top = std::max(top, s + 1);
+        return (uint16_t)s;
+      }
+    }
+  };
+  auto release = [&](uint16_t s) {
+    const int i = s - t.n_zero;
+    used[i >> 6] &= ~(1ull << (i & 63));
+  };
+  // a finish dies before a level's operations when its last reader walked
+  // the level before, or at its last operation
+  auto emit = [&](uint32_t src, uint32_t dst, bool store) {
+    t.op.push_back((src << 8) | ((store ? dst : 1u) << 18) | (store ? 1u << 31 : 0u));
+  };
+  // (read last by a walk: free before the next level's operations)
+  auto place_fin = [&](int u, uint16_t s) {
+    t.fin[u] = s;
+    if (!taken[u] && last_walk[u] >= last_op[u]) dead[std::min(last_walk[u], L) + 1].push_back(s);
+  };
+  std::vector<int32_t> op_left((size_t)N, 0);  // operations at the finish's last level still to come
+  for (int l = 0; l <= L; ++l) {
+    t.ooff.push_back((int32_t)t.op.size());
+    for (uint16_t s : dead[l]) release(s);
+    auto read_op = [&](int u) {  // one operation of level l read u's finish
+      if (last_op[u] == l && --op_left[u] == 0 && last_walk[u] < l) release(t.fin[u]);
+    };
+    auto count = [&](int u) {
+      if (last_op[u] == l) ++op_left[u];
+    };
+    for (int u : wf_at[l]) count(u);
+    if (l < L)
+      for (int v = h.level_off[l]; v < h.level_off[l + 1]; ++v)
+        if (npred_many[v])
+          for (int k = h.pred_off[v]; k < h.pred_off[v + 1]; ++k)
+            if (kind[h.pred_idx[k]] == 3) count(h.pred_idx[k]);
+    // (one store per target: the kernel reads eight sources before it
+    // stores, so a target is never read again in its level's list)
+    std::stable_sort(wf_at[l].begin(), wf_at[l].end(),
+                     [&](int a, int b) { return h.act_wf[a] < h.act_wf[b]; });
+    for (size_t i = 0; i < wf_at[l].size(); ++i) {
+      const int u = wf_at[l][i];
+      const uint32_t s = (uint32_t)(2 + h.act_wf[u]);
+      emit(t.fin[u], 0, false);
+      if (i + 1 == wf_at[l].size() || h.act_wf[wf_at[l][i + 1]] != h.act_wf[u]) emit(s, s, true);
+      read_op(u);
+    }
+    if (l < L) {
+      for (int v = h.level_off[l]; v < h.level_off[l + 1]; ++v) {
+        const int b = h.pred_off[v], e = h.pred_off[v + 1];
+        if (e == b) continue;
+        if (!npred_many[v]) {
+          t.rel[v] = t.fin[h.pred_idx[b]];
+          if (shares[v]) place_fin(v, t.rel[v]);
+          continue;
+        }
+        int pulled = 0;
+        for (int k = b; k < e; ++k) {
+          const int u = h.pred_idx[k];
+          if (kind[u] != 3) continue;
+          emit(t.fin[u], 0, false);
+          ++pulled;
+        }
+        if (pulled) {
+          if (acc_born[v] >= 0) emit(t.rel[v], 0, false);
+          for (int k = b; k < e; ++k)
+            if (kind[h.pred_idx[k]] == 3) read_op(h.pred_idx[k]);
+          if (acc_born[v] < 0) t.rel[v] = alloc();
+          t.op.back() = (t.op.back() & 0x3ff00u) | ((uint32_t)t.rel[v] << 18) | (1u << 31);
+        }
+        if (shares[v])
+          place_fin(v, t.rel[v]);
+        else
+          dead[l + 1].push_back(t.rel[v]);
+      }
+      for (int x : start[l]) {
+        const uint16_t s = alloc();
+        emit(0, s, true);
+        if (x >= N) {
+          t.rel[x - N] = s;
+          for (int k = h.pred_off[x - N]; k < h.pred_off[x - N + 1]; ++k)
+            if (kind[h.pred_idx[k]] == 1) t.fin[h.pred_idx[k]] = s;
+        } else {
+          place_fin(x, s);
+        }
+      }
+    }
+    while (t.op.size() % 8) t.op.push_back(1u << 18);
+  }
+  t.ooff.push_back((int32_t)t.op.size());
+  t.slots = std::max(top, t.n_zero);
+  if (t.op.empty()) t.op.push_back(0);
+  return t;
+}
+
+// A wave's region of the lane-per-plan kernel (n_mut: of generated
+// candidates, else 0); returns its bytes.
+int lanes_layout(const HostWindow& h, wfp::LanesParams& lp, bool keys, int32_t n_mut) {
+  const int words = lp.qbits / 32 + 2 + (keys ? 1 : 0) + (lp.rcap ? 1 : 0);
+  // (order entries: two empty rows after the widest group, one for entries
+  // without a slot)
+  lp.ord = 0;
+  lp.occ = (h.wmax + 4) / 2 * 256;
+  int off = std::max(lp.slots * 256, (lp.rows + 4) / 2 * 256);
+  off = std::max(off, lp.occ + (h.wmax + 31) / 32 * 256);
+  lp.st = off;
+  off += h.D * words * 256;
+  lp.site = off;
+  off += n_mut > 0 ? 2 * n_mut * 256 : 0;
+  lp.site2 = off;
+  off += n_mut > 0 ? 2 * n_mut * 128 : 0;
+  lp.wave_bytes = off;
+  return off;
+}
+
+// Whether the lane-per-plan kernel serves this window, and its tables:
+// uint32 times, the default reclamation order without batch limits, at most
+// 32 models (5-bit queue ids: at most 12 resident at once), and sizes within
+// its packed fields (free memory in 22 bits, order
+// entries of 16 bits).
+void plan_lanes(const wf_plan_ctx* ctx, const HostWindow& h, const wfp::ScoreParams& sp,
+                bool checked, Image& img, wfp::LanesParams& lp) {
+  lp = wfp::LanesParams{};
+  const int N = h.N, D = h.D, M = h.M, W = h.W;
+  if (sp.time64 || sp.nibble < 0 || N < 16 || N > 2044 || D > 64 || M > 32) return;
+  if (M > 16 && !h.rcap.empty()) return;
+  auto bits = [](int n) {  // bits of 0 .. n - 1
+    int b = 0;
+    while ((1 << b) < n) ++b;
+    return b;
+  };
+  if (W - (95 * W + 99) / 100 > 3) return;  // the p95 rank among the four largest
+  const int32_t lim = 1 << 20;
+  for (int m = 0; m < M; ++m)
+    if (h.wmib[m] >= lim) return;
+  for (int d = 0; d < D; ++d)
+    if (h.cap[d] >= lim) return;
+  for (int32_t x : h.mem)
+    if (x >= lim) return;
+  lp.field = M > 16 ? 5 : 4;
+  lp.qbits = M > 16 ? 64 : sp.queue;
+  if (M > 16) {
+    // the most models a device can hold: its initial set, or models whose
+    // weights sum to at most its capacity
+    std::vector<int32_t> w(h.wmib.begin(), h.wmib.begin() + M);
+    std::sort(w.begin(), w.end());
+    for (int d = 0; d < D; ++d) {
+      int k = 0;
+      int64_t sum = 0;
+      while (k < M && sum + w[k] <= h.cap[d]) sum += w[k++];
+      if (std::max(k, __builtin_popcountll(h.init_res[d])) > 12) return;
+    }
+  }
+  const TimeSlots ts = time_slots(h);
+  if (ts.slots > 1023) return;
+  lp.slots = ts.slots;
+  lp.n_zero = ts.n_zero;
+  // consecutive levels are sorted together while they fit the live times'
+  // storage and the entries' index bits (never an entry of all ones: entries
+  // are stored plus 1)
+  const int db = bits(D);
+  auto fits = [&](int n) {
+    return bits(n) + db < 14 || (bits(n) + db == 14 && (n < 1 << bits(n) || D < 1 << db));
+  };
+  if (!fits(h.wmax)) return;
+  const int room = std::max(h.wmax, 2 * ts.slots - 4);
+  std::vector<int32_t> grp;
+  for (int b = h.n_levels; b > 0;) {
+    int a = b - 1;
+    while (a > 0 && h.level_off[b] - h.level_off[a - 1] <= room &&
+           fits(h.level_off[b] - h.level_off[a - 1]))
+      --a;
+    grp.push_back(a);
+    lp.rows = std::max(lp.rows, h.level_off[b] - h.level_off[a]);
+    b = a;
+  }
+  std::reverse(grp.begin(), grp.end());
+  lp.n_grp = (int)grp.size();
+  grp.push_back(h.n_levels);
+  lp.ub = bits(lp.rows);
+  if (!fits(lp.rows)) return;
+  lp.rcap = h.rcap.empty() ? 0 : 1;
+  lp.checked = checked ? 1 : 0;
+  // (what a launch needs besides the tables: looked at with the smallest
+  // region a wave can have)
+  const int tab_lds = N * 16 + M * 16 + (D * M * 4 + 15) / 16 * 16;
+  const int lds_blk = std::min(ctx->lds_per_block, std::min(ctx->lds_per_cu, 160 * 1024));
+  if (tab_lds + 16 + lanes_layout(h, lp, false, 0) > lds_blk) return;
+
+  std::vector<uint32_t> rec((size_t)N * 4), wm((size_t)M * 4, 0), ld((size_t)D * M), act((size_t)N),
+      alv((size_t)N), res0((size_t)D), fr((size_t)D), arr((size_t)std::max(W, 1));
+  for (int f = 0; f < W; ++f) arr[f] = (uint32_t)(h.arrival[f] - sp.origin);
+  for (int d = 0; d < D; ++d) {
+    res0[d] = (uint32_t)h.init_res[d];
+    fr[d] = (uint32_t)(h.free0[d] - sp.origin);
+    for (int m = 0; m < M; ++m) ld[(size_t)d * M + m] = (uint32_t)h.load[(size_t)m * D + d];
+  }
+  const uint64_t ones = lp.field == 4 ? 0x1111111111111111ull : 0x084210842108421ull;
+  for (int m = 0; m < M; ++m) {
+    const uint64_t x = (uint64_t)m * ones;
+    wm[m * 4] = (uint32_t)h.wmib[m];
+    wm[m * 4 + 1] = (uint32_t)x;
+    wm[m * 4 + 2] = (uint32_t)(x >> 32);
+  }
+  std::vector<int32_t> um((size_t)N * D * 2);
+  for (int i = 0; i < N; ++i) {
+    const bool ready = h.pred_off[i] == h.pred_off[i + 1] && h.arrival[h.act_wf[i]] <= 0;
+    const uint32_t c = h.chain_next[i] >= 0 ? (uint32_t)h.chain_next[i] : 0xffffu;
+    const uint32_t base = (uint32_t)h.act_model[i] | ((uint32_t)h.fusible[i] << 6);
+    act[i] = base | (c << 16);
+    rec[(size_t)i * 4] = base | ((uint32_t)ready << 7) | ((uint32_t)h.wf_class[h.act_wf[i]] << 8);
+    rec[(size_t)i * 4 + 1] = arr[h.act_wf[i]];
+    rec[(size_t)i * 4 + 2] = (uint32_t)ts.rel[i] | ((uint32_t)ts.fin[i] << 16);
+    rec[(size_t)i * 4 + 3] = c;
+    for (int d = 0; d < D; ++d) {
+      um[((size_t)d * N + i) * 2] = h.lat[(size_t)i * D + d];
+      um[((size_t)d * N + i) * 2 + 1] = h.mem[(size_t)i * D + d];
+    }
+  }
+  for (int l = 0; l < h.n_levels; ++l)
+    for (int i = h.level_off[l]; i < h.level_off[l + 1]; ++i)
+      alv[i] = (uint32_t)h.level_off[l] | ((uint32_t)(h.level_off[l + 1] - h.level_off[l]) << 16);
+  wfp::LanesTab& t = lp.t;
+  t.rec = img.put(rec.data(), rec.size() * 4);
+  t.wm = img.put(wm.data(), wm.size() * 4);
+  t.ld = img.put(ld.data(), ld.size() * 4);
+  img.bytes.resize(align_up(img.bytes.size(), 16), 0);
+  t.lds_bytes = (int)img.bytes.size();
+  t.um = img.put(um.data(), um.size() * 4);
+  t.act = img.put(act.data(), act.size() * 4);
+  t.alv = img.put(alv.data(), alv.size() * 4);
+  t.op = img.put(ts.op.data(), ts.op.size() * 4);
+  t.ooff = img.put(ts.ooff.data(), ts.ooff.size() * 4);
+  t.loff = img.put(h.level_off.data(), h.level_off.size() * 4);
+  t.grp = img.put(grp.data(), grp.size() * 4);
+  t.cap = img.put(h.cap.data(), h.cap.size() * 4);
+  t.res0 = img.put(res0.data(), res0.size() * 4);
+  t.free0 = img.put(fr.data(), fr.size() * 4);
+  t.arr = img.put(arr.data(), arr.size() * 4);
+  t.wmib = img.put(h.wmib.data(), h.wmib.size() * 4);
+  t.rcap = img.put(h.rcap.data(), h.rcap.size() * 4);
+  img.bytes.resize(align_up(img.bytes.size(), 16), 0);
+  t.bytes = (int)img.bytes.size();
+  lp.ok = 1;
+}
+
 // Plans per wave and waves per workgroup for n plans.  A wave's time hardly
 // falls with fewer waves beside it and is mostly a serial chain (the longest
 // device of its plans, and passes that loop over its plans), so a batch too
@@ -1093,6 +1434,66 @@ wfp::ScoreParams fit_grid(const wf_plan_ctx* ctx, wfp::ScoreParams sp, bool sear
   const int64_t wgs = (groups + sp.waves - 1) / sp.waves;
   if (wgs < sp.grid) sp.grid = (int)wgs;
   return sp;
+}
+
+// Whether the lane-per-plan kernel is the one to take for a batch: when it is
+// expected to be faster than the kernel that gives a lane to each (plan,
+// device).  With g groups of 64 plans per CU, fitted to times on MI355X:
+//   - a wave takes about 0.82 us per activation for its 64 plans when it has a
+//     SIMD to itself (keys 10%, replica caps 15%, every mutation of a generated
+//     candidate 5.5% more), and a CU's waves take rounds; a wave beyond the
+//     four SIMDs counts half, and only over many rounds;
+//   - the other kernels walk a level in as many trips as its busiest lane has
+//     units, over all lanes of a wave: w units on D devices give a lane
+//     a = w / D of them, the busiest of 64 about a + 2.4 sqrt(a) + 0.5.  A
+//     trip of a wave of 64 / D plans is 0.12 us of a CU (the general kernel
+//     0.3; keys 20%, replica caps 10%, a mutation 3.5% more), and more where
+//     LDS holds fewer than eight waves.
+// 256 activations on 8 devices, this kernel against the other: 16,384 plans
+// 197 / 80 us, 65,536 plans 211 / 291 us, 98,304 plans 388 / 355 us, 262,144
+// plans 781 / 896 us, 1,048,576 plans 2,645 / 3,493 us (generated around an
+// incumbent 2,836 / 3,463 us); 96 activations on 4 devices, 32,768 plans
+// 84 / 66 us, 131,072 plans 118 / 260 us; 24 models (general kernel), 65,536
+// plans 212 / 724 us.
+bool lanes_pays(const wf_plan_ctx* ctx, const wfp::LanesParams& lp, int fit, int64_t groups,
+                bool keys, int32_t n_mut) {
+  const HostWindow& h = ctx->host;
+  const wfp::ScoreParams& sp = ctx->dw.sp;
+  const double g = (double)groups / ctx->n_cu;
+  const double simds = std::min(fit, 4), waves = simds + 0.5 * (fit - simds);
+  const double rounds = std::max(1.0, std::min(std::ceil(g / simds), g / waves + 0.5));
+  const double ours = 0.82 * h.N * rounds * (keys ? 1.1 : 1.0) * (lp.rcap ? 1.15 : 1.0) *
+                      (1.0 + 0.055 * n_mut);
+  double trips = 0.0;
+  for (int l = 0; l < h.n_levels; ++l) {
+    const double a = (double)(h.level_off[l + 1] - h.level_off[l]) / h.D;
+    trips += a + 2.4 * std::sqrt(a) + 0.5;
+  }
+  const bool lean = ctx->dw.lean.ok != 0;
+  const int G = std::max(1, 64 / h.D);
+  wfp::LeanOffsets o{};
+  const int held = lean ? (160 * 1024 - ctx->dw.lean.t.lds_bytes) / lean_layout(h, G, sp.nwa, o)
+                        : sp.waves;
+  const double theirs = g * trips * (64.0 / G) * (lean ? 0.12 : 0.3) *
+                        ((!lean && sp.wave_global) || held >= 8 ? 1.0 : 8.0 / std::max(held, 1)) *
+                        (keys ? 1.2 : 1.0) * (lp.rcap ? 1.1 : 1.0) * (1.0 + 0.035 * n_mut);
+  return ours < theirs;
+}
+
+// The lane-per-plan kernel's launch over n plans, when it is the one to take.
+bool lanes_shape(const wf_plan_ctx* ctx, int64_t n, bool keys, int32_t n_mut, wfp::LanesParams& lp) {
+  lp = ctx->dw.lanes;
+  if (!lp.ok || ctx->dw.lanes_force < 0 || n_mut > wfp::kPatchMaxMut) return false;
+  const int lds_blk = std::min(ctx->lds_per_block, std::min(ctx->lds_per_cu, 160 * 1024));
+  const int wb = lanes_layout(ctx->host, lp, keys, n_mut);
+  const int fit = std::min(lp.most, (lds_blk - lp.t.lds_bytes - 16) / wb);
+  if (fit < 1) return false;
+  const int64_t groups = (n + 63) / 64;
+  if (ctx->dw.lanes_force == 0 && !lanes_pays(ctx, lp, fit, groups, keys, n_mut)) return false;
+  lp.waves = (int)std::min<int64_t>(fit, (groups + ctx->n_cu - 1) / ctx->n_cu);
+  lp.grid = (int)std::min<int64_t>((groups + lp.waves - 1) / lp.waves, ctx->n_cu);
+  lp.lds_bytes = lp.t.lds_bytes + 16 + lp.waves * wb;
+  return true;
 }
 
 // Run a scoring launch with the window's parameters, then, for a window
@@ -1193,6 +1594,7 @@ void wf_plan_ctx_destroy(wf_plan_ctx* ctx) {
   (void)hipSetDevice(ctx->device);
   free_device_window(ctx->dw);
   if (ctx->key_work) (void)hipFree(ctx->key_work);
+  if (ctx->lanes_scratch) (void)hipFree(ctx->lanes_scratch);
   (void)hipSetDevice(prev);
   delete ctx;
 }
@@ -1240,44 +1642,47 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   DeviceWindow dw;
-  e = hipMalloc(&dw.tab, img.bytes.size());
+  // every table of the window in one allocation and one copy: an upload is
+  // part of every scheduling tick
+  size_t rule_best_at = 0;
+  const std::vector<unsigned char> rimg = rule_image(h, &rule_best_at);
+  Image limg, nimg;
+  plan_lean(ctx, h, sp, checked, limg, dw.lean);
+  const char* lanes_env = std::getenv("WF_PLAN_LANES");
+  dw.lanes_force = lanes_env && std::strcmp(lanes_env, "on") == 0 ? 1
+                   : (lanes_env && std::strcmp(lanes_env, "off") == 0) || std::getenv("WF_PLAN_KERNEL") ? -1 : 0;
+  if (dw.lanes_force >= 0) plan_lanes(ctx, h, sp, checked, nimg, dw.lanes);
+  std::vector<unsigned char> tables;
+  auto add = [&](const std::vector<unsigned char>& part) {
+    const size_t at = align_up(tables.size(), 256);
+    tables.resize(at + part.size(), 0);
+    std::memcpy(tables.data() + at, part.data(), part.size());
+    return at;
+  };
+  tables.reserve(img.bytes.size() + img64.bytes.size() + rimg.size() + limg.bytes.size() +
+                 nimg.bytes.size() + 5 * 256);
+  const size_t at_tab = add(img.bytes);
+  const size_t at_64 = checked ? add(img64.bytes) : 0;
+  const size_t at_rules = add(rimg);
+  const size_t at_lean = dw.lean.ok ? add(limg.bytes) : 0;
+  const size_t at_lanes = dw.lanes.ok ? add(nimg.bytes) : 0;
+  e = hipMalloc(&dw.tab, tables.size());
   if (e != hipSuccess) {
     (void)hipSetDevice(prev);
     ctx->err = "device allocation of the window failed";
     return WF_ENOMEM;
   }
-  e = hipMemcpy(dw.tab, img.bytes.data(), img.bytes.size(), hipMemcpyHostToDevice);
+  e = hipMemcpy(dw.tab, tables.data(), tables.size(), hipMemcpyHostToDevice);
   if (e != hipSuccess) {
     free_device_window(dw);
     (void)hipSetDevice(prev);
     return hip_fail(ctx, e, "copying the window to the device");
   }
-  if (checked) {
-    e = hipMalloc(&dw.tab64, img64.bytes.size());
-    if (e != hipSuccess) {
-      free_device_window(dw);
-      (void)hipSetDevice(prev);
-      ctx->err = "device allocation of the window failed";
-      return WF_ENOMEM;
-    }
-    e = hipMemcpy(dw.tab64, img64.bytes.data(), img64.bytes.size(), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      free_device_window(dw);
-      (void)hipSetDevice(prev);
-      return hip_fail(ctx, e, "copying the window to the device");
-    }
-  }
-  size_t rule_best_at = 0;
-  const std::vector<unsigned char> rimg = rule_image(h, &rule_best_at);
-  e = hipMalloc(&dw.rules, rimg.size());
-  if (e == hipSuccess) e = hipMemcpy(dw.rules, rimg.data(), rimg.size(), hipMemcpyHostToDevice);
-  if (e != hipSuccess) {
-    free_device_window(dw);
-    (void)hipSetDevice(prev);
-    return hip_fail(ctx, e, "copying the rule tables to the device");
-  }
-  dw.rule_pf = static_cast<const unsigned long long*>(dw.rules);
-  dw.rule_best = static_cast<const int8_t*>(dw.rules) + rule_best_at;
+  const unsigned char* base = static_cast<const unsigned char*>(dw.tab);
+  dw.rule_pf = reinterpret_cast<const unsigned long long*>(base + at_rules);
+  dw.rule_best = reinterpret_cast<const int8_t*>(base + at_rules + rule_best_at);
+  dw.lean.tab = base + at_lean;
+  dw.lanes.tab = base + at_lanes;
   // one scratch area serves every pass (they run in order on a stream)
   wfp::ScoreParams* all[5] = {&sp, &sps, &spsw, &sp64, &sps64};
   size_t need = 0;
@@ -1296,21 +1701,29 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
     for (int i = 0; i < 5; ++i)
       if (all[i]->wave_global) all[i]->scratch = static_cast<unsigned char*>(dw.scratch);
   }
-  sp.tab = static_cast<const unsigned char*>(dw.tab);
-  sps.tab = static_cast<const unsigned char*>(dw.tab);
-  spsw.tab = static_cast<const unsigned char*>(dw.tab);
-  Image limg;
-  plan_lean(ctx, h, sp, checked, limg, dw.lean);
-  if (dw.lean.ok) {
-    e = hipMalloc(&dw.tab_lean, limg.bytes.size());
-    if (e == hipSuccess)
-      e = hipMemcpy(dw.tab_lean, limg.bytes.data(), limg.bytes.size(), hipMemcpyHostToDevice);
-    if (e != hipSuccess) {
-      free_device_window(dw);
-      (void)hipSetDevice(prev);
-      return hip_fail(ctx, e, "copying the lean kernel's tables to the device");
+  sp.tab = sps.tab = spsw.tab = base + at_tab;
+  if (dw.lanes.ok) {
+    // the order of every wave that can run at once, at most 512 MiB
+    const int lds_blk = std::min(ctx->lds_per_block, std::min(ctx->lds_per_cu, 160 * 1024));
+    wfp::LanesParams lp = dw.lanes;
+    const size_t wave = (size_t)ctx->n_cu * (h.N + 4) * 256;
+    dw.lanes.most = std::min({wfp::kLanesWaves, (int)((size_t(1) << 29) / wave),
+                              (lds_blk - lp.t.lds_bytes - 16) / lanes_layout(h, lp, false, 0)});
+    const size_t bytes = dw.lanes.most * wave;
+    if (bytes > ctx->lanes_bytes) {
+      // kept for the next windows; it only grows
+      void* p = nullptr;
+      e = hipMalloc(&p, bytes);
+      if (e == hipSuccess) {
+        if (ctx->lanes_scratch) (void)hipFree(ctx->lanes_scratch);
+        ctx->lanes_scratch = p;
+        ctx->lanes_bytes = bytes;
+      } else {
+        (void)hipGetLastError();
+        dw.lanes.ok = 0;  // (the other kernels serve every call)
+      }
     }
-    dw.lean.tab = static_cast<const unsigned char*>(dw.tab_lean);
+    dw.lanes.scratch = static_cast<unsigned char*>(ctx->lanes_scratch);
   }
   const char* pack = std::getenv("WF_PLAN_PACK");
   dw.pack_full = pack && std::strcmp(pack, "full") == 0;
@@ -1319,8 +1732,7 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
   dw.sp_search_wide = spsw;
   dw.checked = checked;
   if (checked) {
-    sp64.tab = static_cast<const unsigned char*>(dw.tab64);
-    sps64.tab = static_cast<const unsigned char*>(dw.tab64);
+    sp64.tab = sps64.tab = base + at_64;
     dw.sp64 = sp64;
     dw.sp64_search = sps64;
   }
@@ -1347,6 +1759,12 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
   if (std::getenv("WF_PLAN_VERBOSE") && dw.lean.ok)
     std::fprintf(stderr, "[wf_plan] lean kernel: at most %d plans per wave, tables=%d B (%d B in LDS)\n",
                  dw.lean.G, dw.lean.t.bytes, dw.lean.t.lds_bytes);
+  if (std::getenv("WF_PLAN_VERBOSE") && dw.lanes.ok) {
+    wfp::LanesParams lp = dw.lanes;
+    std::fprintf(stderr, "[wf_plan] lane-per-plan kernel: %d live times per plan, wave=%d B, tables=%d B "
+                 "(%d B in LDS), queue %d bits of %d\n", lp.slots, lanes_layout(h, lp, false, 0), lp.t.bytes,
+                 lp.t.lds_bytes, lp.qbits, lp.field);
+  }
   free_device_window(ctx->dw);
   ctx->dw = dw;
   ctx->host = std::move(h);
@@ -1376,7 +1794,14 @@ wf_status wf_plan_score_batch(wf_plan_ctx* ctx, const int8_t* dev, const uint16_
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const DeviceWindow& dw = ctx->dw;
-  if (!sched && dw.lean.ok) {
+  wfp::LanesParams lanes;
+  if (!sched && lanes_shape(ctx, n_plans, false, 0, lanes)) {
+    e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n_plans, scores, nullptr, false,
+                                static_cast<hipStream_t>(hip_stream));
+    if (e == hipSuccess && dw.checked)
+      e = wfp::launch_score(fit_grid(ctx, dw.sp64, false, n_plans), dev, prio, flags, n_plans, scores, nullptr,
+                            nullptr, static_cast<hipStream_t>(hip_stream));
+  } else if (!sched && dw.lean.ok) {
     // the lean kernel, then (times not proven below 2^32) the general fp64
     // pass over the groups holding a plan whose times saturated
     const wfp::LeanParams lp = lean_shape(ctx, n_plans);
@@ -1438,7 +1863,14 @@ wf_status wf_plan_search_batch(wf_plan_ctx* ctx, const int8_t* dev, const uint16
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const wfp::SearchArgs sa = search_params(ctx, mode, seed, n_mut, first);
   const DeviceWindow& dw = ctx->dw;
-  if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper && dw.lean.search_ok &&
+  wfp::LanesParams lanes;
+  if (lanes_shape(ctx, n_candidates, false, n_mut, lanes)) {
+    e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n_candidates, scores, &sa, false,
+                                static_cast<hipStream_t>(hip_stream));
+    if (e == hipSuccess && dw.checked)
+      e = wfp::launch_score(fit_grid(ctx, dw.sp64_search, true, n_candidates), dev, prio, flags, n_candidates,
+                            scores, nullptr, &sa, static_cast<hipStream_t>(hip_stream));
+  } else if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper && dw.lean.search_ok &&
       n_mut <= wfp::kPatchMaxMut) {
     // the lean kernel generates the candidates as the incumbent plus their
     // changed sites; then (times not proven below 2^32) the general fp64
@@ -1557,7 +1989,14 @@ wf_status wf_plan_score_keys(wf_plan_ctx* ctx, const int8_t* dev, const uint16_t
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const DeviceWindow& dw = ctx->dw;
-  if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper) {
+  wfp::LanesParams lanes;
+  if (lanes_shape(ctx, n_plans, true, 0, lanes)) {
+    e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n_plans, keys, nullptr, true,
+                                static_cast<hipStream_t>(hip_stream));
+    if (e == hipSuccess && dw.checked)
+      e = wfp::launch_score_keys(fit_grid(ctx, dw.sp64, false, n_plans), dev, prio, flags, n_plans, keys,
+                                 nullptr, static_cast<hipStream_t>(hip_stream));
+  } else if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper) {
     // the lean kernel's key mode, then the general fp64 pass over the groups
     // holding a plan whose uint32 times saturated
     const wfp::LeanParams lp = lean_shape(ctx, n_plans);
@@ -1591,7 +2030,14 @@ wf_status wf_plan_search_keys(wf_plan_ctx* ctx, const int8_t* dev, const uint16_
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const wfp::SearchArgs sa = search_params(ctx, mode, seed, n_mut, first);
   const DeviceWindow& dw = ctx->dw;
-  if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper && dw.lean.search_ok &&
+  wfp::LanesParams lanes;
+  if (lanes_shape(ctx, n_candidates, true, n_mut, lanes)) {
+    e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n_candidates, keys, &sa, true,
+                                static_cast<hipStream_t>(hip_stream));
+    if (e == hipSuccess && dw.checked)
+      e = wfp::launch_score_keys(fit_grid(ctx, dw.sp64_search, true, n_candidates), dev, prio, flags,
+                                 n_candidates, keys, &sa, static_cast<hipStream_t>(hip_stream));
+  } else if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper && dw.lean.search_ok &&
       n_mut <= wfp::kPatchMaxMut) {
     const wfp::LeanParams lp = lean_shape(ctx, n_candidates);
     e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_candidates, keys, &sa, true,

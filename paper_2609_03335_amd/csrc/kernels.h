@@ -229,6 +229,65 @@ struct LeanParams {
   int paper;       // 1: the paper's reclamation order (plan scores only; qbits -1)
 };
 
+// The lane-per-plan kernel's window tables (lanes.hip), an image like the
+// lean kernel's: the first lds_bytes go into every workgroup's LDS.
+struct LanesTab {
+  // LDS part
+  int rec;     // u32x4 [N]  {activation word (TabOffsets::act), workflow arrival (relative
+               //            time), slot of the release | slot the finish goes to << 16,
+               //            chain successor or 0xffff}
+  int wm;      // u32x4 [M]  {model weights, model id in every queue field (64 bits), 0}
+  int ld;      // u32 [D][M] load time
+  int lds_bytes;
+  // through the cache
+  int um;      // i32x2 [D][N] {run time (-1 ineligible), activation memory}
+  int act;     // u32 [N]    model | fusible << 6 | chain successor << 16
+  int alv;     // u32 [N]    as TabOffsets::alv
+  int op;      // u32        operations before each level: source slot << 8 | target slot << 18 |
+               //            store << 31: the running maximum takes the source and goes to
+               //            the target (without the store bit slot 1, which nobody
+               //            reads); with it, it starts again at 0
+  int ooff;    // i32 [L+2]  first operation of each level; the last list follows the walk
+  int loff;    // i32 [L+1]
+  int grp;     // i32 [G+1]  levels sorted together: the first level of each group, then L
+  int cap;     // i32 [D]
+  int res0;    // u32 [D]
+  int free0;   // u32 [D]
+  int arr;     // u32 [W]
+  int wmib;    // i32 [M]
+  int rcap;    // i32 [M]
+  int bytes;
+};
+
+// Launch plan of the lane-per-plan kernel.  A wave's region: the plans' live
+// times (slot 0 is always 0, slot 1 takes what nobody reads, then the
+// workflows' latest finishes where the p95 rank needs each), then at these
+// offsets the arrays named below, all [entry][64 lanes].
+struct LanesParams {
+  int ok;
+  int checked;     // 1: uint32 additions saturate and flag the plan for the fp64 pass
+  int qbits;       // reclamation queue: 32 or 64 bits
+  int field;       // bits per model id in the queue: 4 or 5 (up to 32 models)
+  int rcap;        // 1: the window caps replicas
+  int ub;          // bits of an activation's index within its group in an order entry
+  int slots;       // live times per plan
+  int n_zero;      // slots that start at 0 (the others are set by an operation)
+  int n_grp, rows; // groups of levels sorted together, the most activations of one
+  int st, occ, ord, site, site2;  // u32 device state; while the order is built, in the live
+                           // times' storage: u32 occupied slots, u16 order entries of a
+                           // level; u32 and u16: candidates' changed sites
+  int wave_bytes;
+  int most;        // waves per workgroup the scratch holds
+  int waves, grid, lds_bytes;
+  const unsigned char* tab;
+  unsigned char* scratch;  // u32 [N + 4][64 lanes] per wave: the resource order (and
+                           // rows that are read ahead)
+  LanesTab t;
+};
+
+// Waves per workgroup of the lane-per-plan kernel.
+constexpr int kLanesWaves = 8;
+
 // Waves per workgroup of the lean kernel: the queue variants, and the
 // paper's order.
 constexpr int kLeanPlainWaves = 10;
@@ -249,6 +308,11 @@ struct SearchArgs;
 hipError_t launch_score_lean(const ScoreParams& sp, const LeanParams& lp, const int8_t* dev,
                              const uint16_t* prio, const uint8_t* flags, int64_t n_plans,
                              void* out, const SearchArgs* search, bool keys, hipStream_t stream);
+
+// The same by the lane-per-plan kernel.
+hipError_t launch_score_lanes(const ScoreParams& sp, const LanesParams& lp, const int8_t* dev,
+                              const uint16_t* prio, const uint8_t* flags, int64_t n_plans,
+                              void* out, const SearchArgs* search, bool keys, hipStream_t stream);
 
 // Internal status bit of a uint32-time pass: some time of the plan reached
 // 2^32 - 1 (saturated), so an fp64 pass rescores it.  Never left in a record

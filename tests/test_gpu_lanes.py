@@ -1,0 +1,90 @@
+"""The lane-per-plan kernel (a wave scores 64 plans, large batches) forced on
+for small ones: scores, ranking keys and generated candidates bytewise against
+the oracle, on windows of every shape it packs differently (ragged level
+widths, fused chains, priorities that are no permutation, 5-bit model ids,
+saturating times, replica caps, p95 among the largest latencies, wide and deep
+levels), at batch sizes around a wave's 64 plans.  Windows it does not serve
+take the other kernels."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2609_03335_amd as pkg
+from paper_2609_03335_amd import workload as W
+
+pytestmark = pytest.mark.gpu
+
+WINDOWS = {
+    "odd": dict(n_wf=6, nodes=(4, 19), n_dev=7, n_models=11),
+    "sixteen": dict(n_wf=2, nodes=(8, 8), n_dev=3, n_models=4),
+    "chains": dict(n_wf=9, nodes=(9, 12), n_dev=5, n_models=3, p_edge=0.2, same_model_bias=0.9),
+    "ranks": dict(n_wf=40, nodes=(6, 16), n_dev=10, n_models=16),
+    "models": dict(n_wf=20, nodes=(6, 16), n_dev=12, n_models=31, q_inel=0.0,
+                   cap_range=(20000, 90000)),
+    "late": dict(n_wf=12, nodes=(6, 16), n_dev=6, n_models=10, load_range=(1 << 29, 1 << 30)),
+    "devices": dict(n_wf=12, nodes=(6, 16), n_dev=60, n_models=10),
+    "one_device": dict(n_wf=5, nodes=(6, 16), n_dev=1, n_models=5),
+    "deep": dict(n_levels=(30, 40), width=(4, 12), n_dev=6, n_models=12),
+}
+
+
+@pytest.mark.parametrize("caps", [False, True])
+@pytest.mark.parametrize("name", sorted(WINDOWS))
+def test_against_oracle(name, caps, monkeypatch):
+    monkeypatch.setenv("WF_PLAN_LANES", "on")
+    for seed, n in ((1, 1), (2, 64), (3, 65), (4, 200)):
+        rng = np.random.default_rng([seed, len(name), caps])
+        gen = W.random_deep_window if name == "deep" else W.random_window
+        win = gen(rng, **WINDOWS[name])
+        win.wf_class = rng.integers(0, 4, win.n_wf).astype(np.uint8)
+        if caps:
+            held = np.array([sum((int(r) >> m) & 1 for r in win.init_resident)
+                             for m in range(win.n_models)])
+            win.model_replica_cap = np.maximum(np.maximum(held, 1), win.n_dev - 1).astype(np.int32)
+        plans = W.random_plans(win, n, rng, p_bad_dev=0.002, prio_mode=("perm", "any")[seed % 2])
+        with pkg.Context(0) as ctx:
+            ctx.wf_plan_upload_window(win)
+            dev, prio, flags = pkg.device_plans(plans, "cuda:0")
+            out = pkg.score_batch(ctx, dev, prio, flags, n)
+            keys = torch.empty((n, 32), dtype=torch.uint8, device="cuda:0")
+            ctx.wf_plan_score_keys(dev, prio, flags, n, keys)
+            torch.cuda.synchronize()
+            assert pkg.scores_to_numpy(out, n).tobytes() == oracle.score(win, plans).tobytes(), (name, n)
+            assert pkg.keys_to_numpy(keys, n).tobytes() == oracle.phi_keys(win, plans).tobytes(), (name, n)
+            for n_mut, mode in ((1, 0), (8, 1)):
+                ctx.wf_plan_search_batch(dev[0], prio[0], flags[0], 77, n_mut, 5, n, out, mode=mode)
+                ctx.wf_plan_search_keys(dev[0], prio[0], flags[0], 77, n_mut, 5, n, keys, mode=mode)
+                torch.cuda.synchronize()
+                cand = W.PlanBatch(*oracle.search_candidates(
+                    win, plans.dev[0], plans.prio[0], plans.flags[0], 77, n_mut, 5, n, mode=mode))
+                assert pkg.scores_to_numpy(out, n).tobytes() == oracle.score(win, cand).tobytes(), \
+                    (name, n, n_mut)
+                assert pkg.keys_to_numpy(keys, n).tobytes() == oracle.phi_keys(win, cand).tobytes(), \
+                    (name, n, n_mut)
+
+
+def test_many_groups_and_kernels_agree(monkeypatch):
+    """More groups than waves at once, a ragged last one, buffers at odd
+    addresses: the same records as the kernel that takes small batches."""
+    rng = np.random.default_rng(9)
+    win = W.random_window(rng, n_wf=3, nodes=(7, 7), n_dev=4, n_models=5)
+    n, N = 64 * 256 * 8 + 64 * 300 + 7, win.n_act
+    base = W.random_plans(win, 4096, rng, prio_mode="perm")
+    pick = rng.integers(0, 4096, n)
+    dev, prio, flags = (torch.from_numpy(np.ascontiguousarray(x[pick]).view(t)).to("cuda:0")
+                        for x, t in ((base.dev, np.int8), (base.prio, np.int16), (base.flags, np.uint8)))
+    room = torch.empty(n * N + 1, dtype=torch.int8, device="cuda:0")
+    room[1:] = dev.reshape(-1)
+    dev = room[1:].view(n, N)
+    got = {}
+    for lanes in ("on", "off"):
+        monkeypatch.setenv("WF_PLAN_LANES", lanes)
+        with pkg.Context(0) as ctx:
+            ctx.wf_plan_upload_window(win)
+            for _ in range(2):
+                out = torch.zeros((n, 32), dtype=torch.uint8, device="cuda:0")
+                ctx.wf_plan_score_batch(dev, prio, flags, n, out)
+                torch.cuda.synchronize()
+                got.setdefault(lanes, []).append(out.cpu())
+    assert all(torch.equal(x, got["off"][0]) for x in got["on"] + got["off"])
