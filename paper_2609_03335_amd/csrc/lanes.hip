@@ -31,8 +31,9 @@
 // 84 live times and 24 words of device state each, so five waves share a CU and
 // each waits for its own LDS reads (about 1,130 cycles per unit against some
 // 130 vector instructions).  2,645 us there against 3,490 us with a lane per
-// (plan, device): 343 GB/s of plan rows and records, 44,000 against 79,000
-// vector lane-instructions per plan.  With the order in LDS (three waves per
+// (plan, device): 343 GB/s of plan rows and records, 49,000 against 79,000
+// vector lane-instructions per plan; the scratch rows triple the HBM traffic
+// (3.6 against 0.91 GB), which the walk hides.  With the order in LDS (three waves per
 // CU) it took 4,482 us.
 #include <type_traits>
 
