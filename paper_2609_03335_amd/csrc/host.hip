@@ -865,7 +865,7 @@ wf_status plan_launch(wf_plan_ctx* ctx, const HostWindow& h, bool search, wfp::S
 }
 
 // Per-wave LDS region of the lean kernel for G plans; returns its size.
-int lean_layout(const HostWindow& h, int G, int nwa, wfp::LeanOffsets& o) {
+int lean_layout(const HostWindow& h, int G, wfp::LeanOffsets& o) {
   size_t off = 0;
   auto take = [&](size_t n) {
     const size_t at = off;
@@ -876,7 +876,7 @@ int lean_layout(const HostWindow& h, int G, int nwa, wfp::LeanOffsets& o) {
   o = wfp::LeanOffsets{};
   o.flags = take((size_t)G * NB);
   o.rec = take((size_t)G * h.N * 2);
-  o.mask = take((size_t)G * h.D * nwa * 8);
+  o.mask = take((size_t)G * h.D * ((h.N + 63) / 64) * 8);
   const size_t last_bytes = (size_t)G * h.D * h.M * 4;
   const bool paper = h.victim_order == WF_VICTIM_PAPER;
   o.fin = take((size_t)G * h.N * 4);
@@ -997,7 +997,7 @@ void plan_lean(wf_plan_ctx* ctx, const HostWindow& h, const wfp::ScoreParams& sp
   const int lds_blk = std::min(ctx->lds_per_block, lds_cu);
   const int G = std::max(1, 64 / D);
   wfp::LeanOffsets o{};
-  const int wb = lean_layout(h, G, sp.nwa, o);
+  const int wb = lean_layout(h, G, o);
   const int fit = (lds_blk - t.lds_bytes) / std::max(wb, 1);
   const int waves = std::min(wfp::kLeanWaves, fit);
   if (waves < 2) return;
@@ -1390,7 +1390,7 @@ wfp::LeanParams lean_shape(const wf_plan_ctx* ctx, int64_t n) {
   const int lds_blk = std::min(ctx->lds_per_block, std::min(ctx->lds_per_cu, 160 * 1024));
   auto wave_bytes = [&](int G) {
     wfp::LeanOffsets o{};
-    return lean_layout(ctx->host, G, ctx->dw.sp.nwa, o);
+    return lean_layout(ctx->host, G, o);
   };
   const int max_waves = lp.paper ? wfp::kLeanWaves : wfp::kLeanPlainWaves;
   auto fit = [&](int G) { return std::min(max_waves, (lds_blk - lp.t.lds_bytes) / wave_bytes(G)); };
@@ -1398,7 +1398,7 @@ wfp::LeanParams lean_shape(const wf_plan_ctx* ctx, int64_t n) {
   lp.G = s.G;
   lp.waves = s.waves;
   lp.grid = s.grid;
-  lp.lds_bytes = lp.t.lds_bytes + s.waves * lean_layout(ctx->host, s.G, ctx->dw.sp.nwa, lp.wo);
+  lp.lds_bytes = lp.t.lds_bytes + s.waves * lean_layout(ctx->host, s.G, lp.wo);
   return lp;
 }
 
@@ -1472,7 +1472,7 @@ bool lanes_pays(const wf_plan_ctx* ctx, const wfp::LanesParams& lp, int fit, int
   const bool lean = ctx->dw.lean.ok != 0;
   const int G = std::max(1, 64 / h.D);
   wfp::LeanOffsets o{};
-  const int held = lean ? (160 * 1024 - ctx->dw.lean.t.lds_bytes) / lean_layout(h, G, sp.nwa, o)
+  const int held = lean ? (160 * 1024 - ctx->dw.lean.t.lds_bytes) / lean_layout(h, G, o)
                         : sp.waves;
   const double theirs = g * trips * (64.0 / G) * (lean ? 0.12 : 0.3) *
                         ((!lean && sp.wave_global) || held >= 8 ? 1.0 : 8.0 / std::max(held, 1)) *

@@ -142,3 +142,25 @@ def test_keys_and_candidates_with_batch_limits(ctx):
     torch.cuda.synchronize()
     cand = W.PlanBatch(*oracle.search_candidates(win, *inc, 23, 2, 0, 700))
     assert pkg.scores_to_numpy(scores, 700).tobytes() == oracle.score(win, cand, threads=THREADS).tobytes()
+
+
+@pytest.mark.parametrize("seed,n_dev,n_models", [(35, 3, 8), (37, 4, 13), (7, 6, 8), (27, 2, 13)])
+def test_deep_windows_with_batch_limits_in_the_lean_kernel(ctx, seed, n_dev, n_models, capfd,
+                                                           monkeypatch):
+    """Windows whose schedules take the ring of recent levels while their plan
+    scores take the lean kernel: that kernel's slot masks cover the whole
+    window, not a level."""
+    rng = np.random.default_rng(seed)
+    win = W.random_deep_window(rng, n_levels=(60, 80), width=(3, 7), n_dev=n_dev, n_models=n_models)
+    win.dev_batch = np.full(n_dev, 3, np.int32)
+    plans = W.random_plans(win, 500, rng, prio_mode=("perm", "any")[seed % 2])
+    monkeypatch.setenv("WF_PLAN_VERBOSE", "1")
+    ctx.wf_plan_upload_window(win)
+    assert "ring of recent levels" in capfd.readouterr().err
+    assert ctx.wf_plan_score_kernel() == "score_lean"
+    dev, prio, flags = pkg.device_plans(plans, "cuda:0")
+    log(f"[batch] deep seed {seed}: N={win.n_act} D={n_dev} M={n_models}")
+    out = pkg.score_batch(ctx, dev, prio, flags, plans.n_plans)
+    torch.cuda.synchronize()
+    assert pkg.scores_to_numpy(out, plans.n_plans).tobytes() == \
+        oracle.score(win, plans, threads=THREADS).tobytes()
