@@ -1209,9 +1209,7 @@ int lanes_layout(const HostWindow& h, wfp::LanesParams& lp, bool keys, int32_t n
   // (order entries: two empty rows after the widest group, one for entries
   // without a slot)
   lp.ord = 0;
-  lp.occ = (h.wmax + 4) / 2 * 256;
   int off = std::max(lp.slots * 256, (lp.rows + 4) / 2 * 256);
-  off = std::max(off, lp.occ + (h.wmax + 31) / 32 * 256);
   lp.st = off;
   off += h.D * words * 256;
   lp.site = off;
@@ -1273,7 +1271,7 @@ void plan_lanes(const wf_plan_ctx* ctx, const HostWindow& h, const wfp::ScorePar
   };
   if (!fits(h.wmax)) return;
   const int room = std::max(h.wmax, 2 * ts.slots - 4);
-  std::vector<int32_t> grp;
+  std::vector<int32_t> grp, run((size_t)h.n_levels, 0);
   for (int b = h.n_levels; b > 0;) {
     int a = b - 1;
     while (a > 0 && h.level_off[b] - h.level_off[a - 1] <= room &&
@@ -1281,6 +1279,11 @@ void plan_lanes(const wf_plan_ctx* ctx, const HostWindow& h, const wfp::ScorePar
       --a;
     grp.push_back(a);
     lp.rows = std::max(lp.rows, h.level_off[b] - h.level_off[a]);
+    // runs of its levels that one lane per activation can rank
+    for (int l = a, e; l < b; l = e) {
+      for (e = l + 1; e < b && h.level_off[e + 1] - h.level_off[l] <= 64; ++e) {}
+      run[l] = e;
+    }
     b = a;
   }
   std::reverse(grp.begin(), grp.end());
@@ -1342,6 +1345,7 @@ void plan_lanes(const wf_plan_ctx* ctx, const HostWindow& h, const wfp::ScorePar
   t.ooff = img.put(ts.ooff.data(), ts.ooff.size() * 4);
   t.loff = img.put(h.level_off.data(), h.level_off.size() * 4);
   t.grp = img.put(grp.data(), grp.size() * 4);
+  t.run = img.put(run.data(), run.size() * 4);
   t.cap = img.put(h.cap.data(), h.cap.size() * 4);
   t.res0 = img.put(res0.data(), res0.size() * 4);
   t.free0 = img.put(fr.data(), fr.size() * 4);

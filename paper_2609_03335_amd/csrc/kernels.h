@@ -250,6 +250,8 @@ struct LanesTab {
   int ooff;    // i32 [L+2]  first operation of each level; the last list follows the walk
   int loff;    // i32 [L+1]
   int grp;     // i32 [G+1]  levels sorted together: the first level of each group, then L
+  int run;     // i32 [L]    of a run's first level: its end (levels of one group, at most 64
+               //            activations or a single level)
   int cap;     // i32 [D]
   int res0;    // u32 [D]
   int free0;   // u32 [D]
@@ -273,9 +275,9 @@ struct LanesParams {
   int slots;       // live times per plan
   int n_zero;      // slots that start at 0 (the others are set by an operation)
   int n_grp, rows; // groups of levels sorted together, the most activations of one
-  int st, occ, ord, site, site2;  // u32 device state; while the order is built, in the live
-                           // times' storage: u32 occupied slots, u16 order entries of a
-                           // level; u32 and u16: candidates' changed sites
+  int st, ord, site, site2;  // u32 device state; while the order is built, in the live
+                           // times' storage: u16 order entries of a group of levels;
+                           // u32 and u16: candidates' changed sites
   int wave_bytes;
   int most;        // waves per workgroup the scratch holds
   int waves, grid, lds_bytes;

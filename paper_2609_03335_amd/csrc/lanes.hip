@@ -185,9 +185,11 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
   const uint32_t* t_op = reinterpret_cast<const uint32_t*>(tg + lp.t.op);
   const Uniform<uint32_t> u_act = uniform_at<uint32_t>(tg, lp.t.act);
   const Uniform<uint32_t> u_alv = uniform_at<uint32_t>(tg, lp.t.alv);
+  const uint32_t* t_alv = reinterpret_cast<const uint32_t*>(tg + lp.t.alv);
   const Uniform<int32_t> u_grp = uniform_at<int32_t>(tg, lp.t.grp);
   const Uniform<int32_t> u_ooff = uniform_at<int32_t>(tg, lp.t.ooff);
   const Uniform<int32_t> u_loff = uniform_at<int32_t>(tg, lp.t.loff);
+  const Uniform<int32_t> u_run = uniform_at<int32_t>(tg, lp.t.run);
   const Uniform<int32_t> u_cap = uniform_at<int32_t>(tg, lp.t.cap);
   const Uniform<uint32_t> u_res0 = uniform_at<uint32_t>(tg, lp.t.res0);
   const Uniform<uint32_t> u_free0 = uniform_at<uint32_t>(tg, lp.t.free0);
@@ -198,7 +200,6 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
   unsigned char* wl = lds + lp.t.lds_bytes + 16 + lp.wave_bytes * wid;
   uint32_t* s_slot = reinterpret_cast<uint32_t*>(wl) + lane;
   uint32_t* s_st = reinterpret_cast<uint32_t*>(wl + lp.st) + lane;
-  uint32_t* s_occ = reinterpret_cast<uint32_t*>(wl + lp.occ) + lane;
   uint16_t* s_ord = reinterpret_cast<uint16_t*>(wl + lp.ord) + lane;
   uint32_t* s_site = reinterpret_cast<uint32_t*>(wl + lp.site) + lane;
 
@@ -294,8 +295,31 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
       const int c8 = u_loff[lv] & ~7;
       return chunk(c8 < N - 8 ? c8 : N - 8);
     };
+    // (of plan b of the wave, read by every lane: activation u's priority,
+    // flag bits and device)
+    struct Gene {
+      uint32_t pr, fb, d;
+    };
+    const int64_t last = P - 1 - grp * 64;  // the group's last plan
+    auto gene_of = [&](int b, int u) -> Gene {
+      if constexpr (SEARCH) {
+        LaneSites sb = sites;
+        sb.p += b - lane;
+        sb.q += b - lane;
+        sb.n = __builtin_amdgcn_readlane(sites.n, b);
+        const int k = sb.find(u);
+        if (k >= 0)
+          return {sb.w(k) >> 16, ((uint32_t)sb.x(k) >> 8) & 3u, (uint32_t)sb.x(k) & 0xffu};
+        return {prio_all[u], ((uint32_t)flags_all[u >> 2] >> ((u & 3) << 1)) & 3u,
+                (uint32_t)(uint8_t)dev_all[u]};
+      } else {
+        const int64_t p = grp * 64 + b;
+        return {prio_all[p * N + u],
+                ((uint32_t)flags_all[p * NB + (u >> 2)] >> ((u & 3) << 1)) & 3u,
+                (uint32_t)(uint8_t)dev_all[p * N + u]};
+      }
+    };
     int at_grp = lp.n_grp - 1, lb = sp.n_levels, la = u_grp[at_grp];
-    bool single = false;  // a group whose priorities are not such a permutation: level by level
     Chunk first = first_of(la);
     while (lb > 0) {
       const int lo = u_loff[la], hi = u_loff[lb], w = hi - lo;
@@ -308,7 +332,7 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
       uint4* o16 = reinterpret_cast<uint4*>(wl + lp.ord);
       for (int i = lane; i < n16; i += 64) o16[i] = make_uint4(0u, 0u, 0u, 0u);
       wsync();
-      int heads = 0;
+      int fused = 0;  // of the lane's plan: activations that are no heads
       auto place = [&](const Chunk& c, int j, uint32_t base, auto plain) {
         const uint32_t d = (uint32_t)(c.dv >> (8 * j)) & 0xffu;
         const uint32_t pr = (uint32_t)((j < 4 ? c.p0 : c.p1) >> (16 * (j & 3))) & 0xffffu;
@@ -318,7 +342,6 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
         at = at < (c.lw[j] >> 16) ? pr - (uint32_t)lo : out;
         if constexpr (decltype(plain)::value) {
           dmax = umax(dmax, d);
-          heads += 64;
         } else {
           const uint32_t a = c.a[j];
           if ((a >> 16) != 0xffffu) {
@@ -328,11 +351,10 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
           }
           if (a & 64u) {
             const bool head = !(fb & 1u);
-            heads += __popcll(__ballot(head));
+            fused += head ? 0 : 1;
             at = head ? at : out;
             dmax = head ? umax(dmax, d) : dmax;
           } else {
-            heads += 64;
             dmax = umax(dmax, d);
           }
         }
@@ -360,7 +382,7 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
       wsync();
       bool ranked;
       {
-        uint32_t mine = 0u;
+        uint32_t mine = (uint32_t)fused;
         for (int i = lane; i < n16; i += 64) {
           const uint4 v = o16[i];
           mine += (uint32_t)((v.x & 0xffffu) != 0u) + (uint32_t)((v.x >> 16) != 0u) +
@@ -368,74 +390,65 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
                   (uint32_t)((v.z & 0xffffu) != 0u) + (uint32_t)((v.z >> 16) != 0u) +
                   (uint32_t)((v.w & 0xffffu) != 0u) + (uint32_t)((v.w >> 16) != 0u);
         }
-        int occupied = 0;
-        for (int b = 0; (8 * ((n16 + 63) >> 6)) >> b; ++b)
-          occupied += __popcll(__ballot((mine >> b) & 1u)) << b;
-        ranked = occupied != heads;
-      }
-      if (ranked && lb - la > 1) {
-        single = true;
-        la = lb - 1;
-        first = first_of(la);
-        continue;
+        int sum = 0;  // occupied rows and fused activations
+        for (int b = 0; (8 * ((n16 + 63) >> 6) + w) >> b; ++b)
+          sum += __popcll(__ballot((mine >> b) & 1u)) << b;
+        ranked = sum != 64 * w;
       }
       if (ranked) {
-        // keys by index instead: priorities, and which are heads
-        for (int i = 0; i < (w + 31) >> 5; ++i) s_occ[i << 6] = 0u;
-        for (int u = lo; u < hi; ++u) {
-          uint32_t pr, fb;
-          if constexpr (SEARCH) {
-            pr = (uint32_t)sites.prio(u);
-            fb = sites.flags(u);
-          } else {
-            pr = rprio[u];
-            fb = (uint32_t)rfl[u >> 2] >> ((u & 3) << 1);
+        // the plans whose priorities are no such permutation, one after the
+        // other by the whole wave: a lane takes an activation of a run of
+        // levels (up to 64 activations, or one wider level in pieces of 64)
+        // and counts the keys below its own: (level, priority, index), a
+        // fused activation behind its level's heads.  (One such plan in a wave
+        // is common where a few percent of the plans are such; ranked by its
+        // own lane alone, it takes w^2 steps per level that every lane waits
+        // for.  131,072 plans of 400 activations in four levels with 2% such
+        // plans: 15,300 us that way, 1,124 us this way, 914 us with none; all
+        // such: 4,810 us, the kernel with a lane per (plan, device) 18,500.)
+        int own = fused;
+        for (int i = 0; i < w; ++i) own += s_ord[i << 6] != 0 ? 1 : 0;
+        for (uint64_t bad = __ballot(own != w && lane <= last); bad; bad &= bad - 1ull) {
+          const int b = __builtin_ctzll(bad);
+          uint16_t* ob = s_ord + (b - lane);
+          for (int lv = la, le; lv < lb; lv = le) {
+            le = u_run[lv];
+            const int l0 = u_loff[lv], rw = u_loff[le] - l0, sh = rw <= 64 ? 6 : 11;
+            auto key_of = [&](int i, uint32_t& e) -> uint32_t {  // e: the row's entry
+              if (i >= rw) return ~0u;
+              const int u = l0 + i;
+              const uint4 r = t_rec[u];
+              const Gene g = gene_of(b, u);
+              const bool chain = r.w != 0xffffu && (gene_of(b, (int)r.w).fb & 1u);
+              const bool member = (r.x & 64u) && (g.fb & 1u);
+              e = member ? 0u
+                         : (uint32_t)(u - lo) + 1u + (umin(g.d, (uint32_t)D - 1u) << ub) +
+                               ((g.fb & 2u) << 13) + (chain ? kChain16 : 0u);
+              const uint32_t lv0 = (t_alv[u] & 0xffffu) - (uint32_t)l0;
+              return (lv0 << 23) | ((member ? 0x10000u : g.pr) << sh) | (uint32_t)i;
+            };
+            for (int c0 = 0; c0 < rw; c0 += 64) {
+              uint32_t e = 0u, e2 = 0u, rank = 0u;
+              const uint32_t key = key_of(c0 + lane, e);
+              for (int c2 = 0; c2 < rw; c2 += 64) {
+                const uint32_t k2 = c2 == c0 ? key : key_of(c2 + lane, e2);
+                const int n = rw - c2 < 64 ? rw - c2 : 64;
+                for (int j0 = 0; j0 < n; j0 += 16)
+#pragma unroll
+                  for (int j = 0; j < 16; ++j)
+                    rank += (uint32_t)__builtin_amdgcn_readlane((int)k2, j0 + j) < key ? 1u : 0u;
+              }
+              if (c0 + lane < rw) ob[(l0 - lo + (int)rank) << 6] = (uint16_t)e;
+            }
           }
-          const uint32_t ul = (uint32_t)(u - lo);
-          s_ord[ul << 6] = (uint16_t)pr;
-          if (!((u_act[u] & 64u) && (fb & 1u))) atomicOr(&s_occ[(ul >> 5) << 6], 1u << (ul & 31u));
         }
         wsync();
       }
       // the next levels, their first rows read ahead
       const int lb2 = la;
-      int la2 = la;
-      if (lb2 > 0) {
-        if (lb2 == u_grp[at_grp]) {
-          --at_grp;
-          single = false;
-          la2 = u_grp[at_grp];
-        } else {
-          la2 = single ? lb2 - 1 : u_grp[at_grp];
-        }
-      }
+      const int la2 = lb2 > 0 ? u_grp[--at_grp] : 0;
       first = first_of(la2);
-      uint32_t prev = 0xffffffffu;  // ranked levels: the last key taken
-      // the unit in row i (ranked: of the largest key below the last one)
-      auto get = [&](int i, auto by_rank) -> uint32_t {
-        if constexpr (!decltype(by_rank)::value) return s_ord[i << 6];
-        uint32_t best = 0u;  // 1 + key
-        for (int s = 0; s < w; ++s) {
-          const uint32_t key = (((uint32_t)s_ord[s << 6] << 14) | (uint32_t)s) + 1u;
-          if (((s_occ[(s >> 5) << 6] >> (s & 31)) & 1u) && key < prev) best = umax(best, key);
-        }
-        prev = best;
-        if (best == 0u) return 0u;
-        const uint32_t ul = (best - 1u) & 0x3fffu;
-        const int u = lo + (int)ul;
-        uint32_t d, fb;
-        if constexpr (SEARCH) {
-          d = (uint32_t)sites.dev(u) & 0xffu;
-          fb = sites.flags(u);
-        } else {
-          d = (uint32_t)(uint8_t)rdev[u];
-          fb = (uint32_t)rfl[u >> 2] >> ((u & 3) << 1);
-        }
-        const uint32_t c = t_rec[u].w;
-        return 1u + (ul | (umin(d, (uint32_t)D - 1u) << ub) | ((fb & 2u) << 13) |
-                     (c != 0xffffu && fuse_of((int)c) ? kChain16 : 0u));
-      };
-      auto rows = [&](auto by_rank) {
+      {
         // the unit after next is read, and the next one's model and its
         // device's mask, while this one is marked
         struct Row {
@@ -462,20 +475,16 @@ __global__ __launch_bounds__(64 * kLanesWaves) void score_lanes(
           if (Q.d == R.d) Q.seen = R.seen;
         };
         Row A, B;
-        fetch(get(w - 1, by_rank), A);
+        fetch(s_ord[(w - 1) << 6], A);
         A.seen = s_st[(A.d * SW) << 6];
-        uint32_t e = w > 1 ? get(w - 2, by_rank) : 0u;
+        uint32_t e = w > 1 ? s_ord[(w - 2) << 6] : 0u;
         for (int i = w - 1; i >= 0; i -= 2) {
-          uint32_t e2 = i > 1 ? get(i - 2, by_rank) : 0u;
+          uint32_t e2 = i > 1 ? s_ord[(i - 2) << 6] : 0u;
           mark(i, e, A, B);
-          e = i > 2 ? get(i - 3, by_rank) : 0u;
+          e = i > 2 ? s_ord[(i - 3) << 6] : 0u;
           if (i > 0) mark(i - 1, e2, B, A);
         }
-      };
-      if (ranked)
-        rows(std::true_type{});
-      else
-        rows(std::false_type{});
+      }
       wsync();
       la = la2;
       lb = lb2;

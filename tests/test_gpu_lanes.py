@@ -88,3 +88,78 @@ def test_many_groups_and_kernels_agree(monkeypatch):
                 torch.cuda.synchronize()
                 got.setdefault(lanes, []).append(out.cpu())
     assert all(torch.equal(x, got["off"][0]) for x in got["on"] + got["off"])
+
+
+def no_permutation(plans, pick, how, rng):
+    """The picked plans' priorities made duplicates, values outside their
+    level's range, or one shared value."""
+    p, n = plans.prio, plans.prio.shape[1]
+    for i in np.flatnonzero(pick):
+        if how == "one_pair":
+            a, b = rng.integers(0, n, 2)
+            p[i, a] = p[i, b]
+        elif how == "any":
+            p[i] = rng.integers(0, 1 << 16, n)
+        else:
+            p[i] = 65535
+    return plans
+
+
+@pytest.mark.parametrize("how", ["one_pair", "any", "equal"])
+@pytest.mark.parametrize("name", ["narrow", "chains", "wide", "wider"])
+def test_some_priorities_are_no_permutation(name, how, monkeypatch):
+    """Plans that are ranked among plans that are not, in levels of few and of
+    many times 64 activations, one or several to a group of levels."""
+    monkeypatch.setenv("WF_PLAN_LANES", "on")
+    kw = {"narrow": dict(n_levels=(9, 12), width=(2, 9), n_dev=6, n_models=12),
+          "chains": dict(n_wf=9, nodes=(9, 12), n_dev=5, n_models=3, p_edge=0.2, same_model_bias=0.9),
+          "wide": dict(n_levels=(3, 3), width=(63, 66), n_dev=5, n_models=9),
+          "wider": dict(n_levels=(2, 2), width=(127, 200), n_dev=9, n_models=7)}[name]
+    gen = W.random_window if name == "chains" else W.random_deep_window
+    for seed, n, share in ((1, 65, 0.02), (2, 130, 0.3), (3, 70, 1.0)):
+        rng = np.random.default_rng([seed, len(name), len(how)])
+        win = gen(rng, **kw)
+        plans = W.random_plans(win, n, rng, p_bad_dev=0.002, prio_mode="perm")
+        pick = rng.random(n) < share
+        pick[[0, n - 1]] = True
+        plans = no_permutation(plans, pick, how, rng)
+        with pkg.Context(0) as ctx:
+            ctx.wf_plan_upload_window(win)
+            dev, prio, flags = pkg.device_plans(plans, "cuda:0")
+            out = pkg.score_batch(ctx, dev, prio, flags, n)
+            torch.cuda.synchronize()
+            assert pkg.scores_to_numpy(out, n).tobytes() == oracle.score(win, plans).tobytes(), (name, how, n)
+            # candidates around an incumbent that is ranked
+            ctx.wf_plan_search_batch(dev[0], prio[0], flags[0], 31, 8, 5, n, out)
+            torch.cuda.synchronize()
+            cand = W.PlanBatch(*oracle.search_candidates(
+                win, plans.dev[0], plans.prio[0], plans.flags[0], 31, 8, 5, n))
+            assert pkg.scores_to_numpy(out, n).tobytes() == oracle.score(win, cand).tobytes(), (name, how, n)
+
+
+def test_a_few_ranked_plans_do_not_slow_a_batch_down(monkeypatch):
+    """2% of the plans without a permutation: most waves hold one.  The whole
+    batch ranked by each lane alone took 16 times as long as a batch of
+    permutations; ranking those plans alone takes less than twice."""
+    monkeypatch.setenv("WF_PLAN_LANES", "on")
+    rng = np.random.default_rng(3)
+    win = W.random_deep_window(rng, n_levels=(4, 4), width=(100, 100), n_dev=8, n_models=12)
+    n = 65536
+    plans = W.random_plans(win, 1024, rng, prio_mode="perm")
+    mixed = no_permutation(plans.take(np.arange(1024)), rng.random(1024) < 0.02, "any", rng)
+    took = []
+    with pkg.Context(0) as ctx:
+        ctx.wf_plan_upload_window(win)
+        out = torch.empty((n, 32), dtype=torch.uint8, device="cuda:0")
+        for batch in (plans, mixed):
+            rows = [x.repeat(n // 1024, 1) for x in pkg.device_plans(batch, "cuda:0")]
+            best = float("inf")
+            for _ in range(4):
+                a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                a.record()
+                ctx.wf_plan_score_batch(*rows, n, out)
+                b.record()
+                torch.cuda.synchronize()
+                best = min(best, a.elapsed_time(b))
+            took.append(best)
+    assert took[1] < 5 * took[0], took
