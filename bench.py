@@ -67,15 +67,6 @@ def measured_counters(config: int, n_plans: int):
     return e
 
 
-def measured_kernel(config: int, n_plans: int):
-    """The kernel the counter record was taken on (large batches take
-    another one than the window's small ones), or None."""
-    if not measured_counters(config, n_plans):
-        return None
-    with open(TRAFFIC_FILE) as f:
-        return json.load(f)["kernel"].rstrip("<")
-
-
 def measured_traffic(config: int, n_plans: int):
     """HBM bytes per scoring launch (FETCH_SIZE + WRITE_SIZE, each scaled by
     the copy-kernel factor), or None."""
@@ -260,7 +251,7 @@ def main():
     traffic = measured_traffic(args.config, P)
     roofline = {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS,
                 "unit": "GB/s", "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": traffic,
-                "kernel": measured_kernel(args.config, P) or ctx.wf_plan_score_kernel(), "kernel_ms": round(kernel_ms, 4),
+                "kernel": ctx.wf_plan_batch_kernel(P), "kernel_ms": round(kernel_ms, 4),
                 "bytes_per_plan": bpp, "copy_gbs_measured": round(copy_gbs, 1),
                 "frac_of_copy": round(achieved / copy_gbs, 4), "argmin_ms": round(argmin_ms, 4)}
 

@@ -410,14 +410,24 @@ wf_status wf_plan_prefix(wf_plan_ctx *ctx, const int8_t *dev, const int64_t *sta
  * every case. */
 int wf_plan_time_bits(const wf_plan_ctx *ctx);
 
-/* Name of the kernel that scores plans read from HBM for the uploaded
- * window without a schedule: "score_lean" when the window qualifies for the
- * lean kernel (uint32 times, at most 16 models, at most 512 activations;
- * under the paper's reclamation order or with batch limits only without
- * replica caps, and not both), else "score_plans"; "" when ctx is NULL or
- * has no window.  Both give identical results.  Under the paper's order or
- * with batch limits the lean kernel serves wf_plan_score_batch only. */
+/* Name of the kernel that scores small batches of plans read from HBM for
+ * the uploaded window without a schedule: "score_lean" when the window
+ * qualifies for the lean kernel (uint32 times, at most 16 models, at most 512
+ * activations; under the paper's reclamation order or with batch limits only
+ * without replica caps, and not both), else "score_plans"; "" when ctx is
+ * NULL or has no window.  Under the paper's order or with batch limits the
+ * lean kernel serves wf_plan_score_batch only.  Large batches of many windows
+ * take a third kernel, "score_lanes": wf_plan_batch_kernel names the one a
+ * call would take.  All give identical results. */
 const char *wf_plan_score_kernel(const wf_plan_ctx *ctx);
+
+/* Name of the kernel that a call for n_plans plans of the uploaded window
+ * would take: plans read from HBM (n_mut < 0: wf_plan_score_batch without a
+ * schedule, or with keys != 0 wf_plan_score_keys) or candidates of n_mut
+ * mutations (wf_plan_search_batch, wf_plan_search_keys).  "" when ctx is NULL,
+ * has no window, or n_plans < 1. */
+const char *wf_plan_batch_kernel(const wf_plan_ctx *ctx, int64_t n_plans, int32_t keys,
+                                 int32_t n_mut);
 
 /* Library version string. */
 const char *wf_plan_version(void);

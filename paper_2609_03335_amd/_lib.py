@@ -46,7 +46,8 @@ EXPORTS = ("wf_plan_ctx_create", "wf_plan_ctx_destroy", "wf_plan_last_error",
            "wf_plan_validate_window", "wf_plan_upload_window", "wf_plan_score_batch",
            "wf_plan_argmin", "wf_plan_argmin_noalloc", "wf_plan_search_batch", "wf_plan_search_rows",
            "wf_plan_score_keys", "wf_plan_search_keys", "wf_plan_argmin_keys",
-           "wf_plan_prefix", "wf_plan_time_bits", "wf_plan_score_kernel", "wf_plan_version")
+           "wf_plan_prefix", "wf_plan_time_bits", "wf_plan_score_kernel",
+           "wf_plan_batch_kernel", "wf_plan_version")
 
 
 class WFError(RuntimeError):
@@ -128,6 +129,8 @@ def load(path: Optional[str] = None) -> ctypes.CDLL:
     lib.wf_plan_time_bits.restype = i32
     lib.wf_plan_score_kernel.argtypes = [vp]
     lib.wf_plan_score_kernel.restype = ctypes.c_char_p
+    lib.wf_plan_batch_kernel.argtypes = [vp, i64, i32, i32]
+    lib.wf_plan_batch_kernel.restype = ctypes.c_char_p
     lib.wf_plan_version.argtypes = []
     lib.wf_plan_version.restype = ctypes.c_char_p
     # an entry point without a declared signature would take Python ints as
@@ -362,6 +365,10 @@ class Context:
 
     def wf_plan_score_kernel(self) -> str:
         return self.lib.wf_plan_score_kernel(self.handle).decode()
+
+    def wf_plan_batch_kernel(self, n_plans: int, keys: bool = False, n_mut: int = -1) -> str:
+        """The kernel a call for n_plans plans takes (n_mut >= 0: generated candidates)."""
+        return self.lib.wf_plan_batch_kernel(self.handle, int(n_plans), int(keys), int(n_mut)).decode()
 
     def close(self):
         if getattr(self, "handle", None):

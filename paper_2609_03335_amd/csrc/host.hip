@@ -1500,17 +1500,53 @@ bool lanes_shape(const wf_plan_ctx* ctx, int64_t n, bool keys, int32_t n_mut, wf
   return true;
 }
 
-// Run a scoring launch with the window's parameters, then, for a window
-// whose uint32 times are not proven safe, the fp64 pass over the groups it
-// flagged (same stream, so in order).  Generated candidates with more than
-// kPatchMaxMut mutations take the layout that holds whole rows.
-template <typename F>
-hipError_t two_pass(const wf_plan_ctx* ctx, bool search, int64_t n, F&& launch, int32_t n_mut = 0) {
+// The kernel that serves a scoring call of n plans: stored ones or, with
+// search, candidates of n_mut mutations each; schedules are the general
+// kernel's.  `lanes`: the lane-per-plan kernel's launch, where it is taken.
+enum class Kernel { kLanes, kLean, kGeneral };
+Kernel pick_kernel(const wf_plan_ctx* ctx, int64_t n, bool sched, bool keys, bool search,
+                   int32_t n_mut, wfp::LanesParams& lanes) {
+  const wfp::LeanParams& lean = ctx->dw.lean;
+  if (sched) return Kernel::kGeneral;
+  if (lanes_shape(ctx, n, keys, n_mut, lanes)) return Kernel::kLanes;
+  if (!lean.ok || ((keys || search) && (lean.batch || lean.paper))) return Kernel::kGeneral;
+  if (search && (!lean.search_ok || n_mut > wfp::kPatchMaxMut)) return Kernel::kGeneral;
+  return Kernel::kLean;
+}
+
+// Scores (wf_plan_score [n]) or, with keys, ranking keys (wf_plan_key [n]) of
+// n plans, or (search) of candidates around the incumbent rows.  For a window
+// whose uint32 times are not proven safe, the general kernel's fp64 pass over
+// the groups with a flagged plan follows (same stream, so in order).
+// Generated candidates with more than kPatchMaxMut mutations take the general
+// kernel's layout that holds whole rows.
+hipError_t launch_plans(const wf_plan_ctx* ctx, const int8_t* dev, const uint16_t* prio,
+                        const uint8_t* flags, int64_t n, void* out, const wf_plan_sched* sched,
+                        const wfp::SearchArgs* search, bool keys, void* hip_stream) {
   const DeviceWindow& dw = ctx->dw;
-  const wfp::ScoreParams& s =
-      !search ? dw.sp : (n_mut <= wfp::kPatchMaxMut ? dw.sp_search : dw.sp_search_wide);
-  hipError_t e = launch(fit_grid(ctx, s, search, n));
-  if (e == hipSuccess && dw.checked) e = launch(fit_grid(ctx, search ? dw.sp64_search : dw.sp64, search, n));
+  const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
+  const int32_t n_mut = search ? search->n_mut : 0;
+  auto general = [&](const wfp::ScoreParams& s) {
+    const wfp::ScoreParams sp = fit_grid(ctx, s, search != nullptr, n);
+    return keys ? wfp::launch_score_keys(sp, dev, prio, flags, n, static_cast<wf_plan_key*>(out),
+                                         search, stream)
+                : wfp::launch_score(sp, dev, prio, flags, n, static_cast<wf_plan_score*>(out),
+                                    sched, search, stream);
+  };
+  wfp::LanesParams lanes;
+  hipError_t e;
+  switch (pick_kernel(ctx, n, sched != nullptr, keys, search != nullptr, n_mut, lanes)) {
+    case Kernel::kLanes:
+      e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n, out, search, keys, stream);
+      break;
+    case Kernel::kLean:
+      e = wfp::launch_score_lean(dw.sp, lean_shape(ctx, n), dev, prio, flags, n, out, search, keys,
+                                 stream);
+      break;
+    default:
+      e = general(!search ? dw.sp : n_mut <= wfp::kPatchMaxMut ? dw.sp_search : dw.sp_search_wide);
+  }
+  if (e == hipSuccess && dw.checked) e = general(search ? dw.sp64_search : dw.sp64);
   return e;
 }
 
@@ -1528,6 +1564,17 @@ int wf_plan_time_bits(const wf_plan_ctx* ctx) {
 const char* wf_plan_score_kernel(const wf_plan_ctx* ctx) {
   if (!ctx || !ctx->has_window) return "";
   return ctx->dw.lean.ok ? "score_lean" : "score_plans";
+}
+
+const char* wf_plan_batch_kernel(const wf_plan_ctx* ctx, int64_t n_plans, int32_t keys,
+                                 int32_t n_mut) {
+  if (!ctx || !ctx->has_window || n_plans < 1) return "";
+  wfp::LanesParams lanes;
+  switch (pick_kernel(ctx, n_plans, false, keys != 0, n_mut >= 0, std::max(n_mut, 0), lanes)) {
+    case Kernel::kLanes: return "score_lanes";
+    case Kernel::kLean: return "score_lean";
+    default: return "score_plans";
+  }
 }
 
 const char* wf_plan_last_error(const wf_plan_ctx* ctx) {
@@ -1797,29 +1844,7 @@ wf_status wf_plan_score_batch(wf_plan_ctx* ctx, const int8_t* dev, const uint16_
   (void)hipGetDevice(&prev);
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
-  const DeviceWindow& dw = ctx->dw;
-  wfp::LanesParams lanes;
-  if (!sched && lanes_shape(ctx, n_plans, false, 0, lanes)) {
-    e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n_plans, scores, nullptr, false,
-                                static_cast<hipStream_t>(hip_stream));
-    if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score(fit_grid(ctx, dw.sp64, false, n_plans), dev, prio, flags, n_plans, scores, nullptr,
-                            nullptr, static_cast<hipStream_t>(hip_stream));
-  } else if (!sched && dw.lean.ok) {
-    // the lean kernel, then (times not proven below 2^32) the general fp64
-    // pass over the groups holding a plan whose times saturated
-    const wfp::LeanParams lp = lean_shape(ctx, n_plans);
-    e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_plans, scores, nullptr, false,
-                               static_cast<hipStream_t>(hip_stream));
-    if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score(fit_grid(ctx, dw.sp64, false, n_plans), dev, prio, flags, n_plans, scores, nullptr,
-                            nullptr, static_cast<hipStream_t>(hip_stream));
-  } else {
-    e = two_pass(ctx, false, n_plans, [&](const wfp::ScoreParams& sp) {
-      return wfp::launch_score(sp, dev, prio, flags, n_plans, scores, sched, nullptr,
-                               static_cast<hipStream_t>(hip_stream));
-    });
-  }
+  e = launch_plans(ctx, dev, prio, flags, n_plans, scores, sched, nullptr, false, hip_stream);
   (void)hipSetDevice(prev);
   if (e != hipSuccess) return hip_fail(ctx, e, "launching the scoring kernel");
   return WF_OK;
@@ -1866,34 +1891,7 @@ wf_status wf_plan_search_batch(wf_plan_ctx* ctx, const int8_t* dev, const uint16
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const wfp::SearchArgs sa = search_params(ctx, mode, seed, n_mut, first);
-  const DeviceWindow& dw = ctx->dw;
-  wfp::LanesParams lanes;
-  if (lanes_shape(ctx, n_candidates, false, n_mut, lanes)) {
-    e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n_candidates, scores, &sa, false,
-                                static_cast<hipStream_t>(hip_stream));
-    if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score(fit_grid(ctx, dw.sp64_search, true, n_candidates), dev, prio, flags, n_candidates,
-                            scores, nullptr, &sa, static_cast<hipStream_t>(hip_stream));
-  } else if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper && dw.lean.search_ok &&
-      n_mut <= wfp::kPatchMaxMut) {
-    // the lean kernel generates the candidates as the incumbent plus their
-    // changed sites; then (times not proven below 2^32) the general fp64
-    // pass over the groups holding a candidate whose times saturated
-    const wfp::LeanParams lp = lean_shape(ctx, n_candidates);
-    e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_candidates, scores, &sa, false,
-                               static_cast<hipStream_t>(hip_stream));
-    if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score(fit_grid(ctx, dw.sp64_search, true, n_candidates), dev, prio, flags, n_candidates,
-                            scores, nullptr, &sa, static_cast<hipStream_t>(hip_stream));
-  } else {
-    e = two_pass(
-        ctx, true, n_candidates,
-        [&](const wfp::ScoreParams& sp) {
-          return wfp::launch_score(sp, dev, prio, flags, n_candidates, scores, nullptr, &sa,
-                                   static_cast<hipStream_t>(hip_stream));
-        },
-        n_mut);
-  }
+  e = launch_plans(ctx, dev, prio, flags, n_candidates, scores, nullptr, &sa, false, hip_stream);
   (void)hipSetDevice(prev);
   if (e != hipSuccess) return hip_fail(ctx, e, "launching the scoring kernel");
   return WF_OK;
@@ -1992,29 +1990,7 @@ wf_status wf_plan_score_keys(wf_plan_ctx* ctx, const int8_t* dev, const uint16_t
   (void)hipGetDevice(&prev);
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
-  const DeviceWindow& dw = ctx->dw;
-  wfp::LanesParams lanes;
-  if (lanes_shape(ctx, n_plans, true, 0, lanes)) {
-    e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n_plans, keys, nullptr, true,
-                                static_cast<hipStream_t>(hip_stream));
-    if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score_keys(fit_grid(ctx, dw.sp64, false, n_plans), dev, prio, flags, n_plans, keys,
-                                 nullptr, static_cast<hipStream_t>(hip_stream));
-  } else if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper) {
-    // the lean kernel's key mode, then the general fp64 pass over the groups
-    // holding a plan whose uint32 times saturated
-    const wfp::LeanParams lp = lean_shape(ctx, n_plans);
-    e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_plans, keys, nullptr, true,
-                               static_cast<hipStream_t>(hip_stream));
-    if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score_keys(fit_grid(ctx, dw.sp64, false, n_plans), dev, prio, flags, n_plans, keys,
-                                 nullptr, static_cast<hipStream_t>(hip_stream));
-  } else {
-    e = two_pass(ctx, false, n_plans, [&](const wfp::ScoreParams& sp) {
-      return wfp::launch_score_keys(sp, dev, prio, flags, n_plans, keys, nullptr,
-                                    static_cast<hipStream_t>(hip_stream));
-    });
-  }
+  e = launch_plans(ctx, dev, prio, flags, n_plans, keys, nullptr, nullptr, true, hip_stream);
   (void)hipSetDevice(prev);
   if (e != hipSuccess) return hip_fail(ctx, e, "launching the ranking-key kernel");
   return WF_OK;
@@ -2033,31 +2009,7 @@ wf_status wf_plan_search_keys(wf_plan_ctx* ctx, const int8_t* dev, const uint16_
   hipError_t e = hipSetDevice(ctx->device);
   if (e != hipSuccess) return hip_fail(ctx, e, "hipSetDevice");
   const wfp::SearchArgs sa = search_params(ctx, mode, seed, n_mut, first);
-  const DeviceWindow& dw = ctx->dw;
-  wfp::LanesParams lanes;
-  if (lanes_shape(ctx, n_candidates, true, n_mut, lanes)) {
-    e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n_candidates, keys, &sa, true,
-                                static_cast<hipStream_t>(hip_stream));
-    if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score_keys(fit_grid(ctx, dw.sp64_search, true, n_candidates), dev, prio, flags,
-                                 n_candidates, keys, &sa, static_cast<hipStream_t>(hip_stream));
-  } else if (dw.lean.ok && !dw.lean.batch && !dw.lean.paper && dw.lean.search_ok &&
-      n_mut <= wfp::kPatchMaxMut) {
-    const wfp::LeanParams lp = lean_shape(ctx, n_candidates);
-    e = wfp::launch_score_lean(dw.sp, lp, dev, prio, flags, n_candidates, keys, &sa, true,
-                               static_cast<hipStream_t>(hip_stream));
-    if (e == hipSuccess && dw.checked)
-      e = wfp::launch_score_keys(fit_grid(ctx, dw.sp64_search, true, n_candidates), dev, prio, flags,
-                                 n_candidates, keys, &sa, static_cast<hipStream_t>(hip_stream));
-  } else {
-    e = two_pass(
-        ctx, true, n_candidates,
-        [&](const wfp::ScoreParams& sp) {
-          return wfp::launch_score_keys(sp, dev, prio, flags, n_candidates, keys, &sa,
-                                        static_cast<hipStream_t>(hip_stream));
-        },
-        n_mut);
-  }
+  e = launch_plans(ctx, dev, prio, flags, n_candidates, keys, nullptr, &sa, true, hip_stream);
   (void)hipSetDevice(prev);
   if (e != hipSuccess) return hip_fail(ctx, e, "launching the ranking-key kernel");
   return WF_OK;

@@ -326,6 +326,7 @@ def test_noalloc_argmin_argument_errors_without_gpu():
 
 def test_score_kernel_without_window():
     assert _lib.load().wf_plan_score_kernel(None) == b""
+    assert _lib.load().wf_plan_batch_kernel(None, 1 << 20, 0, -1) == b""
 
 
 @pytest.mark.parametrize("D", [65, 96, 127])
