@@ -3,8 +3,8 @@ for small ones: scores, ranking keys and generated candidates bytewise against
 the oracle, on windows of every shape it packs differently (ragged level
 widths, fused chains, priorities that are no permutation, 5-bit model ids,
 saturating times, replica caps, p95 among the largest latencies, wide and deep
-levels), at batch sizes around a wave's 64 plans.  Windows it does not serve
-take the other kernels."""
+levels), at batch sizes around a wave's 64 plans.  Each test asserts which
+kernel a call takes: windows it does not serve take the other kernels."""
 import numpy as np
 import pytest
 import torch
@@ -24,9 +24,28 @@ WINDOWS = {
                    cap_range=(20000, 90000)),
     "late": dict(n_wf=12, nodes=(6, 16), n_dev=6, n_models=10, load_range=(1 << 29, 1 << 30)),
     "devices": dict(n_wf=12, nodes=(6, 16), n_dev=60, n_models=10),
+    "five_bits": dict(n_wf=20, nodes=(6, 16), n_dev=5, n_models=31, q_inel=0.0, resident=False,
+                      w_range=(3000, 3010), mem_range=(0, 300), cap_range=(9000, 20000)),
+    "thirteen": dict(n_wf=20, nodes=(6, 16), n_dev=5, n_models=31, q_inel=0.0, resident=False,
+                     w_range=(3000, 3010), mem_range=(0, 300), cap_range=(9000, 20000)),
+    "checked": dict(n_wf=4, nodes=(4, 8), n_dev=2, n_models=5, resident=False,
+                    lat_range=(int(1.4e7), int(7e7)), load_range=(int(1.4e8), int(4.2e8)),
+                    cap_range=(9000, 14000), w_range=(4000, 7000)),
     "one_device": dict(n_wf=5, nodes=(6, 16), n_dev=1, n_models=5),
     "deep": dict(n_levels=(30, 40), width=(4, 12), n_dev=6, n_models=12),
 }
+# windows the kernel does not serve: 13 models and more fit a device, times
+# past 8 x 2^32; and replica caps with 5-bit ids
+FALLBACK = {("models", False), ("models", True), ("thirteen", False), ("thirteen", True),
+            ("late", False), ("late", True), ("five_bits", True)}
+
+
+def window(name, rng):
+    gen = W.random_deep_window if name == "deep" else W.random_window
+    win = gen(rng, **WINDOWS[name])
+    if name in ("five_bits", "thirteen"):  # device 0 holds the 12 (13) smallest models, no more
+        win.dev_cap_mib[0] = np.sort(win.model_mib)[:12 + (name == "thirteen")].sum() + 450
+    return win
 
 
 @pytest.mark.parametrize("caps", [False, True])
@@ -35,8 +54,7 @@ def test_against_oracle(name, caps, monkeypatch):
     monkeypatch.setenv("WF_PLAN_LANES", "on")
     for seed, n in ((1, 1), (2, 64), (3, 65), (4, 200)):
         rng = np.random.default_rng([seed, len(name), caps])
-        gen = W.random_deep_window if name == "deep" else W.random_window
-        win = gen(rng, **WINDOWS[name])
+        win = window(name, rng)
         win.wf_class = rng.integers(0, 4, win.n_wf).astype(np.uint8)
         if caps:
             held = np.array([sum((int(r) >> m) & 1 for r in win.init_resident)
@@ -45,6 +63,11 @@ def test_against_oracle(name, caps, monkeypatch):
         plans = W.random_plans(win, n, rng, p_bad_dev=0.002, prio_mode=("perm", "any")[seed % 2])
         with pkg.Context(0) as ctx:
             ctx.wf_plan_upload_window(win)
+            assert ctx.wf_plan_time_bits() == (64 if name == "late" else 32)
+            for is_keys in (False, True):
+                for n_mut in (-1, 1, 8):
+                    assert (ctx.wf_plan_batch_kernel(n, is_keys, n_mut) == "score_lanes") == \
+                        ((name, caps) not in FALLBACK), (name, caps, n)
             dev, prio, flags = pkg.device_plans(plans, "cuda:0")
             out = pkg.score_batch(ctx, dev, prio, flags, n)
             keys = torch.empty((n, 32), dtype=torch.uint8, device="cuda:0")
@@ -82,6 +105,7 @@ def test_many_groups_and_kernels_agree(monkeypatch):
         monkeypatch.setenv("WF_PLAN_LANES", lanes)
         with pkg.Context(0) as ctx:
             ctx.wf_plan_upload_window(win)
+            assert (ctx.wf_plan_batch_kernel(n) == "score_lanes") == (lanes == "on")
             for _ in range(2):
                 out = torch.zeros((n, 32), dtype=torch.uint8, device="cuda:0")
                 ctx.wf_plan_score_batch(dev, prio, flags, n, out)
@@ -125,6 +149,7 @@ def test_some_priorities_are_no_permutation(name, how, monkeypatch):
         plans = no_permutation(plans, pick, how, rng)
         with pkg.Context(0) as ctx:
             ctx.wf_plan_upload_window(win)
+            assert ctx.wf_plan_batch_kernel(n) == ctx.wf_plan_batch_kernel(n, n_mut=8) == "score_lanes"
             dev, prio, flags = pkg.device_plans(plans, "cuda:0")
             out = pkg.score_batch(ctx, dev, prio, flags, n)
             torch.cuda.synchronize()
@@ -150,6 +175,7 @@ def test_a_few_ranked_plans_do_not_slow_a_batch_down(monkeypatch):
     took = []
     with pkg.Context(0) as ctx:
         ctx.wf_plan_upload_window(win)
+        assert ctx.wf_plan_batch_kernel(n) == "score_lanes"
         out = torch.empty((n, 32), dtype=torch.uint8, device="cuda:0")
         for batch in (plans, mixed):
             rows = [x.repeat(n // 1024, 1) for x in pkg.device_plans(batch, "cuda:0")]
@@ -163,3 +189,44 @@ def test_a_few_ranked_plans_do_not_slow_a_batch_down(monkeypatch):
                 best = min(best, a.elapsed_time(b))
             took.append(best)
     assert took[1] < 5 * took[0], took
+
+
+def test_five_bit_queue_fills_up():
+    """The 5-bit window above really holds 12 models on a device: loads minus
+    reclaimed models over a plan's units there (no model is resident at first)."""
+    rng = np.random.default_rng([4, len("five_bits"), False])
+    win = window("five_bits", rng)
+    plans = W.random_plans(win, 200, rng, prio_mode="perm")
+    _, (_, _, load, _, gone) = oracle.score(win, plans, schedule=True, reclaims=True)
+    on0 = plans.dev == 0
+    held = ((load >= 0) & on0).sum(axis=1) - \
+        np.where(on0, np.vectorize(lambda x: int(x).bit_count() if hasattr(int, "bit_count")
+                                   else bin(int(x)).count("1"))(gone), 0).sum(axis=1)
+    assert held.max() == 12
+
+
+def test_checked_times_saturate_in_some_plans():
+    """The checked window's batch has plans on both sides of 2^32 us."""
+    rng = np.random.default_rng([4, len("checked"), False])
+    win = window("checked", rng)
+    plans = W.random_plans(win, 200, rng, prio_mode="perm")
+    sc, (_, finish, _, _) = oracle.score(win, plans, schedule=True)
+    origin = min(int(win.wf_arrival_us.min()), int(win.dev_free0_us.min()))
+    late = (finish.max(axis=1) - origin)[(sc["status"] & 1) == 0] >= (1 << 32) - 1
+    assert 0.05 < late.mean() < 0.95, late.mean()
+
+
+def test_one_context_over_windows_of_different_size(monkeypatch):
+    """The scratch area is kept from upload to upload: small, larger, not
+    served, small windows of one context, each against the oracle."""
+    monkeypatch.setenv("WF_PLAN_LANES", "on")
+    rng = np.random.default_rng(6)
+    with pkg.Context(0) as ctx:
+        for name in ("sixteen", "ranks", "late", "odd", "deep", "five_bits", "sixteen"):
+            win = window(name, rng)
+            plans = W.random_plans(win, 150, rng, prio_mode="any")
+            ctx.wf_plan_upload_window(win)
+            assert (ctx.wf_plan_batch_kernel(150) == "score_lanes") == (name != "late")
+            out = pkg.score_batch(ctx, *pkg.device_plans(plans, "cuda:0"), 150)
+            torch.cuda.synchronize()
+            assert pkg.scores_to_numpy(out, 150).tobytes() == oracle.score(win, plans).tobytes(), name

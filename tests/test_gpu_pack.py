@@ -31,6 +31,10 @@ WINDOWS = {
     "deep16": (W.random_deep_window, dict(n_levels=(30, 40), width=(4, 12), n_dev=16, n_models=9)),
     "late": (W.random_window, dict(n_wf=12, nodes=(6, 16), n_dev=6, n_models=10,
                                    load_range=(1 << 29, 1 << 30))),
+    "checked": (W.random_window, dict(n_wf=4, nodes=(4, 8), n_dev=2, n_models=5, resident=False,
+                                      lat_range=(int(1.4e7), int(7e7)),
+                                      load_range=(int(1.4e8), int(4.2e8)),
+                                      cap_range=(9000, 14000), w_range=(4000, 7000))),
     "devices": (W.random_window, dict(n_wf=12, nodes=(6, 16), n_dev=90, n_models=10)),
 }
 MODES = ("default", "caps", "paper", "batch", "paper_batch")
@@ -56,6 +60,8 @@ def check(win, rng, n, tag):
     N, D = win.n_act, win.n_dev
     with pkg.Context(0) as ctx:
         ctx.wf_plan_upload_window(win)
+        # ("late" passes 8 x 2^32 us: fp64 times; "checked" takes the two passes)
+        assert ctx.wf_plan_time_bits() == (64 if tag[0] == "late" else 32)
         dev, prio, flags = pkg.device_plans(plans, "cuda:0")
         ref, sched_ref = oracle.score(win, plans, schedule=True)
         live = (ref["status"] & 1) == 0
