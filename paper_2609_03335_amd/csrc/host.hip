@@ -241,6 +241,7 @@ struct DeviceWindow {
   // the lane-per-plan kernel, for large batches
   wfp::LanesParams lanes{};
   int lanes_force = 0;          // WF_PLAN_LANES: 1 = on (any batch), -1 = off
+  double trips = 0.0;           // window_trips, for the choice between the kernels
   // WF_PLAN_PACK=full: every launch takes the most plans per wave (tests use
   // it to cover small batches in the shape of large ones)
   bool pack_full = false;
@@ -1440,51 +1441,67 @@ wfp::ScoreParams fit_grid(const wf_plan_ctx* ctx, wfp::ScoreParams sp, bool sear
   return sp;
 }
 
-// Whether the lane-per-plan kernel is the one to take for a batch: when it is
-// expected to be faster than the kernel that gives a lane to each (plan,
-// device).  With g groups of 64 plans per CU, fitted to times on MI355X:
-//   - a wave takes about 0.82 us per activation for its 64 plans when it has a
-//     SIMD to itself (keys 10%, replica caps 15%, every mutation of a generated
-//     candidate 5.5% more), and a CU's waves take rounds; a wave beyond the
-//     four SIMDs counts half, and only over many rounds;
-//   - the other kernels walk a level in as many trips as its busiest lane has
-//     units, over all lanes of a wave: w units on D devices give a lane
-//     a = w / D of them, the busiest of 64 about a + 2.4 sqrt(a) + 0.5.  A
-//     trip of a wave of 64 / D plans is 0.12 us of a CU (the general kernel
-//     0.3; keys 20%, replica caps 10%, a mutation 3.5% more), and more where
-//     LDS holds fewer than eight waves.
-// 256 activations on 8 devices, this kernel against the other: 16,384 plans
-// 197 / 80 us, 65,536 plans 211 / 291 us, 98,304 plans 388 / 355 us, 262,144
-// plans 781 / 896 us, 1,048,576 plans 2,645 / 3,493 us (generated around an
-// incumbent 2,836 / 3,463 us); 96 activations on 4 devices, 32,768 plans
-// 84 / 66 us, 131,072 plans 118 / 260 us; 24 models (general kernel), 65,536
-// plans 212 / 724 us.
-bool lanes_pays(const wf_plan_ctx* ctx, const wfp::LanesParams& lp, int fit, int64_t groups,
-                bool keys, int32_t n_mut) {
-  const HostWindow& h = ctx->host;
-  const wfp::ScoreParams& sp = ctx->dw.sp;
-  const double g = (double)groups / ctx->n_cu;
-  const double simds = std::min(fit, 4), waves = simds + 0.5 * (fit - simds);
-  const double rounds = std::max(1.0, std::min(std::ceil(g / simds), g / waves + 0.5));
-  const double ours = 0.82 * h.N * rounds * (keys ? 1.1 : 1.0) * (lp.rcap ? 1.15 : 1.0) *
-                      (1.0 + 0.055 * n_mut);
+// What a launch of the kernels with a lane per (plan, device) takes, in us:
+// a wave's work for its G plans is counted in trips of the walk (a level takes
+// as many as the busiest of the wave's lanes has units, window_trips), and
+//   trips + level * levels + group + mut * n_mut
+//     + G / 64 * (unit * N + edge * edges + table * D * M + plan_mut * n_mut)
+// times 1.08 for keys and 1.1 for replica caps, times trip * (1 + share * waves
+// per CU), times the rounds the waves take, plus `fixed`.
+struct Cost {
+  double fixed, trip, share, unit, edge, level, group, table, mut, plan_mut;
+};
+// Fitted to times on MI355X of 190 windows (16 to 1,500 activations, layered,
+// agent and deep, 1 to 64 devices, 2 to 32 models, with and without replica
+// caps), each with 4,096 to 262,144 plans, scores, keys and candidates of 1 to
+// 8 mutations; nine in ten times near the line within 20% (HBM: 45%).
+constexpr Cost kLeanCost{1.87, 0.436, 0.050, 0.99, 0.19, 1.36, 6.5, 0.51, 2.2, 20.6};
+constexpr Cost kLdsCost{5.6, 0.653, 0.097, 0.90, 0.10, 0.27, 0, 0.12, 0, 0};
+constexpr Cost kLdsSearchCost{6.2, 0.297, 0.151, 2.44, 0.21, 1.08, 7.1, 0, 0.53, 8.7};
+constexpr Cost kHbmCost{1.0, 0.695, 0.149, 0.93, 2.25, 0, 0, 0, 0, 0};
+constexpr Cost kRingCost{1.0, 0.366, 0.238, 2.91, 0, 0, 0, 0, 0, 0};
+
+// Trips of the walk over all levels: w units on D devices give a lane w / D of
+// them, the busiest of 64 lanes about 0.83 * sqrt(2 ln 64) = 2.4 standard
+// deviations more, at most all.
+double window_trips(const HostWindow& h) {
+  const double dev = 0.83 * std::sqrt(2.0 * std::log(std::max(2, std::max(1, 64 / h.D) * h.D)));
   double trips = 0.0;
   for (int l = 0; l < h.n_levels; ++l) {
-    const double a = (double)(h.level_off[l + 1] - h.level_off[l]) / h.D;
-    trips += a + 2.4 * std::sqrt(a) + 0.5;
+    const double w = h.level_off[l + 1] - h.level_off[l], a = w / h.D;
+    trips += std::max(1.0, std::min(w, a + dev * std::sqrt(a) + 0.5));
   }
-  const bool lean = ctx->dw.lean.ok != 0;
-  const int G = std::max(1, 64 / h.D);
-  wfp::LeanOffsets o{};
-  const int held = lean ? (160 * 1024 - ctx->dw.lean.t.lds_bytes) / lean_layout(h, G, o)
-                        : sp.waves;
-  const double theirs = g * trips * (64.0 / G) * (lean ? 0.12 : 0.3) *
-                        ((!lean && sp.wave_global) || held >= 8 ? 1.0 : 8.0 / std::max(held, 1)) *
-                        (keys ? 1.2 : 1.0) * (lp.rcap ? 1.1 : 1.0) * (1.0 + 0.035 * n_mut);
-  return ours < theirs;
+  return trips;
 }
 
-// The lane-per-plan kernel's launch over n plans, when it is the one to take.
+double grouped_us(const wf_plan_ctx* ctx, const Cost& c, int G, int waves, int grid, int64_t n,
+                  bool keys, int32_t n_mut) {
+  const HostWindow& h = ctx->host;
+  const double r = (double)((n + G - 1) / G) / ((double)grid * waves);
+  const double per_cu = (double)((grid + ctx->n_cu - 1) / ctx->n_cu) * waves;
+  const double work = ctx->dw.trips + c.level * h.n_levels + c.group + c.mut * n_mut +
+                      G / 64.0 * (c.unit * h.N + c.edge * h.pred_off[h.N] +
+                                  c.table * h.D * h.M + c.plan_mut * n_mut);
+  return c.fixed + work * (keys ? 1.08 : 1.0) * (h.rcap.empty() ? 1.0 : 1.1) * c.trip *
+                       (1.0 + c.share * per_cu) *
+                       (r <= 1.0 ? 1.0 : std::min(std::ceil(r), r + 0.8));
+}
+
+// The same for the lane-per-plan kernel (99 in 100 times within 18%): a wave
+// alone takes 0.68 us per activation for its 64 plans, a wave beside it 3%
+// more, one that shares its SIMD another 6%.
+double lanes_us(const wf_plan_ctx* ctx, const wfp::LanesParams& lp, int64_t groups, bool keys,
+                int32_t n_mut) {
+  const HostWindow& h = ctx->host;
+  const double work = (0.679 * h.N + 0.37 * h.n_levels + 0.177 * h.D + 0.0308 * h.pred_off[h.N]) *
+                          (keys ? 1.112 : 1.0) * (lp.rcap ? 1.067 : 1.0) +
+                      n_mut * (4.7 + 0.0174 * h.N);
+  const double share = 1.0 + 0.055 * std::max(0, lp.waves - 4) + 0.031 * (std::min(lp.waves, 4) - 1);
+  const double r = (double)groups / ((double)lp.waves * lp.grid);
+  return 6.9 + work * share * (r <= 1.0 ? 1.0 : std::min(std::ceil(r), r + 0.56));
+}
+
+// The lane-per-plan kernel's launch over n plans, when it serves the call.
 bool lanes_shape(const wf_plan_ctx* ctx, int64_t n, bool keys, int32_t n_mut, wfp::LanesParams& lp) {
   lp = ctx->dw.lanes;
   if (!lp.ok || ctx->dw.lanes_force < 0 || n_mut > wfp::kPatchMaxMut) return false;
@@ -1493,60 +1510,92 @@ bool lanes_shape(const wf_plan_ctx* ctx, int64_t n, bool keys, int32_t n_mut, wf
   const int fit = std::min(lp.most, (lds_blk - lp.t.lds_bytes - 16) / wb);
   if (fit < 1) return false;
   const int64_t groups = (n + 63) / 64;
-  if (ctx->dw.lanes_force == 0 && !lanes_pays(ctx, lp, fit, groups, keys, n_mut)) return false;
   lp.waves = (int)std::min<int64_t>(fit, (groups + ctx->n_cu - 1) / ctx->n_cu);
   lp.grid = (int)std::min<int64_t>((groups + lp.waves - 1) / lp.waves, ctx->n_cu);
   lp.lds_bytes = lp.t.lds_bytes + 16 + lp.waves * wb;
   return true;
 }
 
-// The kernel that serves a scoring call of n plans: stored ones or, with
+// The kernel that serves a scoring call of n plans -- stored ones or, with
 // search, candidates of n_mut mutations each; schedules are the general
-// kernel's.  `lanes`: the lane-per-plan kernel's launch, where it is taken.
+// kernel's -- and its launch.  The lane-per-plan kernel is taken where it is
+// expected to be faster than the kernel that would run instead, by a tenth,
+// which covers most of the estimates' error: over those windows' 8,062 calls
+// it is taken where it is more than 5% slower in 19 (at most 19%), and a gain
+// of more than 5% is left in 281; over 3,858 calls of 75 other windows in 7 (at
+// most 8%) and 128.  score_lanes / the other, us: 256 activations on 8
+// devices, 65,536 plans 211 / 291 (score_lean); 400 activations of agents,
+// keys of 65,536 plans 700 / 707 (score_lean); 48 activations, 24 models, keys
+// of 16,384 candidates of 8 mutations 91 / 47 (general, LDS); 512 activations
+// of 16 levels, 24 models, 16,384 plans 526 / 398 and 65,536 plans 561 / 1,570
+// (general, ring); 1,000 activations of agents, 32 models, 16,384 plans 712 /
+// 1,689 (general, HBM).
 enum class Kernel { kLanes, kLean, kGeneral };
-Kernel pick_kernel(const wf_plan_ctx* ctx, int64_t n, bool sched, bool keys, bool search,
-                   int32_t n_mut, wfp::LanesParams& lanes) {
-  const wfp::LeanParams& lean = ctx->dw.lean;
-  if (sched) return Kernel::kGeneral;
-  if (lanes_shape(ctx, n, keys, n_mut, lanes)) return Kernel::kLanes;
-  if (!lean.ok || ((keys || search) && (lean.batch || lean.paper))) return Kernel::kGeneral;
-  if (search && (!lean.search_ok || n_mut > wfp::kPatchMaxMut)) return Kernel::kGeneral;
-  return Kernel::kLean;
+struct Choice {
+  Kernel kernel;
+  wfp::LanesParams lanes;
+  wfp::LeanParams lean;
+  wfp::ScoreParams sp;  // the general kernel's
+};
+Choice pick_kernel(const wf_plan_ctx* ctx, int64_t n, bool sched, bool keys, bool search,
+                   int32_t n_mut) {
+  const DeviceWindow& dw = ctx->dw;
+  Choice c{};
+  const bool lanes = !sched && lanes_shape(ctx, n, keys, n_mut, c.lanes);
+  c.kernel = Kernel::kLanes;
+  if (lanes && dw.lanes_force > 0) return c;
+  const Cost* cost;
+  if (!sched && dw.lean.ok && !((keys || search) && (dw.lean.batch || dw.lean.paper)) &&
+      !(search && (!dw.lean.search_ok || n_mut > wfp::kPatchMaxMut))) {
+    c.kernel = Kernel::kLean;
+    c.lean = lean_shape(ctx, n);
+    cost = &kLeanCost;
+  } else {
+    // (more than kPatchMaxMut mutations take the layout that holds whole rows)
+    c.kernel = Kernel::kGeneral;
+    c.sp = fit_grid(ctx, !search ? dw.sp : n_mut <= wfp::kPatchMaxMut ? dw.sp_search : dw.sp_search_wide,
+                    search, n);
+    cost = c.sp.ring == 1 ? &kRingCost : c.sp.wave_global ? &kHbmCost : search ? &kLdsSearchCost : &kLdsCost;
+  }
+  if (lanes) {
+    const bool lean = c.kernel == Kernel::kLean;
+    const double other = grouped_us(ctx, *cost, lean ? c.lean.G : c.sp.G, lean ? c.lean.waves : c.sp.waves,
+                                    lean ? c.lean.grid : c.sp.grid, n, keys, n_mut);
+    if (1.1 * lanes_us(ctx, c.lanes, (n + 63) / 64, keys, n_mut) < other) c.kernel = Kernel::kLanes;
+  }
+  return c;
 }
 
 // Scores (wf_plan_score [n]) or, with keys, ranking keys (wf_plan_key [n]) of
 // n plans, or (search) of candidates around the incumbent rows.  For a window
 // whose uint32 times are not proven safe, the general kernel's fp64 pass over
 // the groups with a flagged plan follows (same stream, so in order).
-// Generated candidates with more than kPatchMaxMut mutations take the general
-// kernel's layout that holds whole rows.
 hipError_t launch_plans(const wf_plan_ctx* ctx, const int8_t* dev, const uint16_t* prio,
                         const uint8_t* flags, int64_t n, void* out, const wf_plan_sched* sched,
                         const wfp::SearchArgs* search, bool keys, void* hip_stream) {
   const DeviceWindow& dw = ctx->dw;
   const hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   const int32_t n_mut = search ? search->n_mut : 0;
-  auto general = [&](const wfp::ScoreParams& s) {
-    const wfp::ScoreParams sp = fit_grid(ctx, s, search != nullptr, n);
+  auto general = [&](const wfp::ScoreParams& sp) {
     return keys ? wfp::launch_score_keys(sp, dev, prio, flags, n, static_cast<wf_plan_key*>(out),
                                          search, stream)
                 : wfp::launch_score(sp, dev, prio, flags, n, static_cast<wf_plan_score*>(out),
                                     sched, search, stream);
   };
-  wfp::LanesParams lanes;
+  const Choice c = pick_kernel(ctx, n, sched != nullptr, keys, search != nullptr, n_mut);
   hipError_t e;
-  switch (pick_kernel(ctx, n, sched != nullptr, keys, search != nullptr, n_mut, lanes)) {
+  switch (c.kernel) {
     case Kernel::kLanes:
-      e = wfp::launch_score_lanes(dw.sp, lanes, dev, prio, flags, n, out, search, keys, stream);
+      e = wfp::launch_score_lanes(dw.sp, c.lanes, dev, prio, flags, n, out, search, keys, stream);
       break;
     case Kernel::kLean:
-      e = wfp::launch_score_lean(dw.sp, lean_shape(ctx, n), dev, prio, flags, n, out, search, keys,
-                                 stream);
+      e = wfp::launch_score_lean(dw.sp, c.lean, dev, prio, flags, n, out, search, keys, stream);
       break;
     default:
-      e = general(!search ? dw.sp : n_mut <= wfp::kPatchMaxMut ? dw.sp_search : dw.sp_search_wide);
+      e = general(c.sp);
   }
-  if (e == hipSuccess && dw.checked) e = general(search ? dw.sp64_search : dw.sp64);
+  if (e == hipSuccess && dw.checked)
+    e = general(fit_grid(ctx, search ? dw.sp64_search : dw.sp64, search != nullptr, n));
   return e;
 }
 
@@ -1569,8 +1618,7 @@ const char* wf_plan_score_kernel(const wf_plan_ctx* ctx) {
 const char* wf_plan_batch_kernel(const wf_plan_ctx* ctx, int64_t n_plans, int32_t keys,
                                  int32_t n_mut) {
   if (!ctx || !ctx->has_window || n_plans < 1) return "";
-  wfp::LanesParams lanes;
-  switch (pick_kernel(ctx, n_plans, false, keys != 0, n_mut >= 0, std::max(n_mut, 0), lanes)) {
+  switch (pick_kernel(ctx, n_plans, false, keys != 0, n_mut >= 0, std::max(n_mut, 0)).kernel) {
     case Kernel::kLanes: return "score_lanes";
     case Kernel::kLean: return "score_lean";
     default: return "score_plans";
@@ -1778,6 +1826,7 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
   }
   const char* pack = std::getenv("WF_PLAN_PACK");
   dw.pack_full = pack && std::strcmp(pack, "full") == 0;
+  dw.trips = dw.lanes.ok ? window_trips(h) : 0.0;
   dw.sp = sp;
   dw.sp_search = sps;
   dw.sp_search_wide = spsw;
