@@ -1588,9 +1588,12 @@ hipError_t launch_plans(const wf_plan_ctx* ctx, const int8_t* dev, const uint16_
     case Kernel::kLanes:
       e = wfp::launch_score_lanes(dw.sp, c.lanes, dev, prio, flags, n, out, search, keys, stream);
       break;
-    case Kernel::kLean:
-      e = wfp::launch_score_lean(dw.sp, c.lean, dev, prio, flags, n, out, search, keys, stream);
+    case Kernel::kLean: {
+      wfp::ScoreParams sp = dw.sp;
+      sp.nwa = (sp.N + 63) / 64;  // its masks cover the whole window (the ring layout's a level)
+      e = wfp::launch_score_lean(sp, c.lean, dev, prio, flags, n, out, search, keys, stream);
       break;
+    }
     default:
       e = general(c.sp);
   }

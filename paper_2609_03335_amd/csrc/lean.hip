@@ -137,8 +137,7 @@ void score_lean(ScoreParams sp, LeanParams lp,
   static_assert(!PAPER || (!SEARCH && !PHI && !RCAP && !BATCH), "the paper's order: plan scores only");
   extern __shared__ __align__(16) unsigned char lds[];
   const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
-  const int N = sp.N, W = sp.W, M = sp.M, D = sp.D, NB = sp.NB, G = lp.G;
-  const int NWA = (N + 63) >> 6;  // the whole window's slots (the ring layout's sp.nwa covers a level)
+  const int N = sp.N, W = sp.W, M = sp.M, D = sp.D, NB = sp.NB, G = lp.G, NWA = sp.nwa;
 
   // ---- window tables: the per-unit ones in LDS, the rest through the cache ----
   {
