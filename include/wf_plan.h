@@ -56,7 +56,8 @@
  *     context must not run concurrently on different streams: the scoring
  *     calls may share the context's scratch areas (per-wave regions of
  *     windows too large for LDS, at most 1 GiB, and of large batches, at most
- *     512 MiB and kept from upload to upload; both allocated at upload) and
+ *     512 MiB, kept from upload to upload and shrunk after 16 uploads in a row
+ *     that need less than a quarter; both allocated at upload) and
  *     the argmins its work area.  A new upload must not race with queued
  *     work either (synchronise first).  Use one context per stream for
  *     concurrent scoring.

@@ -259,10 +259,11 @@ struct wf_plan_ctx {
   HostWindow host;
   DeviceWindow dw;
   void* key_work = nullptr;  // partial results of the argmins
-  // the lane-per-plan kernel's resource orders; grows with the windows
-  // uploaded, freed with the context
+  // the lane-per-plan kernel's resource orders (lanes_area); freed with the
+  // context
   void* lanes_scratch = nullptr;
   size_t lanes_bytes = 0;
+  int lanes_idle = 0;  // uploads in a row that needed less than a quarter of it
 };
 
 namespace {
@@ -276,6 +277,29 @@ void free_device_window(DeviceWindow& dw) {
   if (dw.tab) (void)hipFree(dw.tab);
   if (dw.scratch) (void)hipFree(dw.scratch);
   dw = DeviceWindow{};
+}
+
+// The lane-per-plan kernel's scratch area for the window being uploaded (the
+// upload's last step: nothing that fails after it leaves the former window
+// without).  It grows at once, the old area given back first, and is kept for
+// the next windows, as an allocation costs a fair part of an upload; after
+// kLanesIdle uploads in a row that need less than a quarter of it, it shrinks.
+constexpr int kLanesIdle = 16;
+bool lanes_area(wf_plan_ctx* ctx, size_t need) {
+  ctx->lanes_idle = need < ctx->lanes_bytes / 4 ? ctx->lanes_idle + 1 : 0;
+  if (need <= ctx->lanes_bytes && ctx->lanes_idle < kLanesIdle) return true;
+  if (ctx->lanes_scratch) (void)hipFree(ctx->lanes_scratch);
+  ctx->lanes_scratch = nullptr;
+  ctx->lanes_bytes = 0;
+  ctx->lanes_idle = 0;
+  if (need == 0) return true;
+  if (hipMalloc(&ctx->lanes_scratch, need) != hipSuccess) {
+    (void)hipGetLastError();
+    ctx->lanes_scratch = nullptr;
+    return false;
+  }
+  ctx->lanes_bytes = need;
+  return true;
 }
 
 // The rule tables of the candidate generator (Algorithm 1, Sec. 3.5), as a
@@ -1804,6 +1828,7 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
       if (all[i]->wave_global) all[i]->scratch = static_cast<unsigned char*>(dw.scratch);
   }
   sp.tab = sps.tab = spsw.tab = base + at_tab;
+  size_t order_bytes = 0;
   if (dw.lanes.ok) {
     // the order of every wave that can run at once, at most 512 MiB
     const int lds_blk = std::min(ctx->lds_per_block, std::min(ctx->lds_per_cu, 160 * 1024));
@@ -1811,22 +1836,10 @@ wf_status wf_plan_upload_window(wf_plan_ctx* ctx, const wf_window_desc* w) {
     const size_t wave = (size_t)ctx->n_cu * (h.N + 4) * 256;
     dw.lanes.most = std::min({wfp::kLanesWaves, (int)((size_t(1) << 29) / wave),
                               (lds_blk - lp.t.lds_bytes - 16) / lanes_layout(h, lp, false, 0)});
-    const size_t bytes = dw.lanes.most * wave;
-    if (bytes > ctx->lanes_bytes) {
-      // kept for the next windows; it only grows
-      void* p = nullptr;
-      e = hipMalloc(&p, bytes);
-      if (e == hipSuccess) {
-        if (ctx->lanes_scratch) (void)hipFree(ctx->lanes_scratch);
-        ctx->lanes_scratch = p;
-        ctx->lanes_bytes = bytes;
-      } else {
-        (void)hipGetLastError();
-        dw.lanes.ok = 0;  // (the other kernels serve every call)
-      }
-    }
-    dw.lanes.scratch = static_cast<unsigned char*>(ctx->lanes_scratch);
+    order_bytes = dw.lanes.most * wave;
   }
+  if (!lanes_area(ctx, order_bytes)) dw.lanes.ok = 0;  // (the other kernels serve every call)
+  dw.lanes.scratch = static_cast<unsigned char*>(ctx->lanes_scratch);
   const char* pack = std::getenv("WF_PLAN_PACK");
   dw.pack_full = pack && std::strcmp(pack, "full") == 0;
   dw.trips = dw.lanes.ok ? window_trips(h) : 0.0;

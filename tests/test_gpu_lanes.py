@@ -230,3 +230,24 @@ def test_one_context_over_windows_of_different_size(monkeypatch):
             out = pkg.score_batch(ctx, *pkg.device_plans(plans, "cuda:0"), 150)
             torch.cuda.synchronize()
             assert pkg.scores_to_numpy(out, 150).tobytes() == oracle.score(win, plans).tobytes(), name
+
+
+def test_the_scratch_area_is_given_back():
+    """A large window's scratch area (some 400 MiB) does not stay with a
+    context that uploads small windows from then on."""
+    rng = np.random.default_rng(8)
+    small = window("sixteen", rng)
+    big = W.random_deep_window(rng, n_levels=(40, 40), width=(50, 50), n_dev=4, n_models=6)
+    free = lambda: torch.cuda.mem_get_info(0)[0]
+    with pkg.Context(0) as ctx:
+        ctx.wf_plan_upload_window(small)
+        before = free()
+        ctx.wf_plan_upload_window(big)
+        assert before - free() > 200 << 20
+        for _ in range(20):
+            ctx.wf_plan_upload_window(small)
+        assert before - free() < 100 << 20
+        plans = W.random_plans(small, 100, rng)
+        out = pkg.score_batch(ctx, *pkg.device_plans(plans, "cuda:0"), 100)
+        torch.cuda.synchronize()
+        assert pkg.scores_to_numpy(out, 100).tobytes() == oracle.score(small, plans).tobytes()
