@@ -6,16 +6,20 @@
 // many trips as its busiest device has units, over all plans of the wave --
 // 73 trips for 8 plans of 256 activations on 8 devices, 44% of the lane-trips
 // working.  A lane per plan has one unit per trip in every lane, table
-// indices of the order sweep and of the releases are wave-uniform, and every
-// LDS array is [entry][lane], free of bank conflicts whatever the entry.  The
-// price is LDS: 64 plans' state per wave, so few waves per CU fit, and each
-// wave hides its latency by reading a unit's tables and its device's state
-// one unit ahead.  Batches too small for that take the other kernels.
+// indices of the order sweep and of the releases are wave-uniform, and the
+// plans' LDS arrays are [entry][lane], free of bank conflicts whatever the
+// entry.  (The window's tables are not: each lane gathers them by its own
+// unit, model or device, and those reads conflict: SQ_LDS_BANK_CONFLICT counts
+// 183 M over the 93 M LDS instructions of the workload below.)
+// The price is LDS: 64 plans' state per wave, so few waves per CU fit, and
+// each wave hides its latency by reading a unit's tables and its device's
+// state one unit ahead.  Batches too small for that take the other kernels.
 //
 // Per group of 64 plans:
 //   1. the resource order (Eq. 10) is built level by level, the last one
 //      first: slot = priority when the heads' priorities are distinct values
-//      of the level's index range, else by (priority, index); a unit is marked
+//      of the level's index range, else by (priority, index), which the whole
+//      wave ranks for the plans that need it; a unit is marked
 //      when no later one uses its model on its device, which the walk, first
 //      level first, could not know.  The order goes to a scratch area in HBM
 //      ([slot][lane], read back as whole rows): in LDS it and the unit counts
@@ -32,9 +36,9 @@
 // each waits for its own LDS reads (about 1,130 cycles per unit against some
 // 130 vector instructions).  2,645 us there against 3,490 us with a lane per
 // (plan, device): 343 GB/s of plan rows and records, 49,000 against 79,000
-// vector lane-instructions per plan; the scratch rows triple the HBM traffic
-// (3.6 against 0.91 GB), which the walk hides.  With the order in LDS (three waves per
-// CU) it took 4,482 us.
+// vector lane-instructions per plan; with the scratch rows the HBM traffic is
+// four times the rows and records (3.6 against 0.91 GB), which the walk hides.
+// With the order in LDS (three waves per CU) it took 4,482 us.
 #include <type_traits>
 
 #include "kernels.h"
