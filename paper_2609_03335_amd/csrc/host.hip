@@ -1553,7 +1553,8 @@ bool lanes_shape(const wf_plan_ctx* ctx, int64_t n, bool keys, int32_t n_mut, wf
 // of 16,384 candidates of 8 mutations 91 / 47 (general, LDS); 512 activations
 // of 16 levels, 24 models, 16,384 plans 526 / 398 and 65,536 plans 561 / 1,570
 // (general, ring); 1,000 activations of agents, 32 models, 16,384 plans 712 /
-// 1,689 (general, HBM).
+// 1,689 (general, HBM).  Plans whose priorities are no permutation are not in
+// the estimates: both sides rank them, score_lanes for less (lanes.hip).
 enum class Kernel { kLanes, kLean, kGeneral };
 struct Choice {
   Kernel kernel;
